@@ -86,7 +86,7 @@ struct Builder {
 
   static constexpr int kBins = 64;
   static constexpr int kSpatialBins = 32;
-  static constexpr uint32_t kLeafMax = 2;
+  static constexpr uint32_t kLeafMax = kLeafMaxTris;
 
   struct Split {
     double cost = 1e300;

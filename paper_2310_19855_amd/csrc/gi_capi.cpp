@@ -560,7 +560,12 @@ gi_status gi_build_bvh(gi_context* c, const float* h_verts, uint32_t n_verts, co
     GI_TRY_HIP(c, dalloc(&c->d_tris, tris.size()));
     GI_TRY_HIP(c, dalloc(&c->d_tnrm, tn.size()));
     GI_TRY_HIP(c, dalloc(&c->d_mats, mats.size()));
-    GI_TRY_HIP(c, dalloc(&c->d_dyn, 3 * (size_t)gi::kMaxDyn));
+    GI_TRY_HIP(c, dalloc(&c->d_dyn, 2 + 3 * (size_t)gi::kMaxDyn));
+    // on the device an empty child's planes are NaN: no slab test passes, so none checks for it
+    for (Node4& nd : nodes)
+      for (int k = 0; k < 4; ++k)
+        if (nd.child[k] == gi::kNodeEmpty)
+          nd.lox[k] = nd.hix[k] = nd.loy[k] = nd.hiy[k] = nd.loz[k] = nd.hiz[k] = std::nanf("");
     GI_TRY_HIP(c, hipMemcpy(c->d_nodes, nodes.data(), sizeof(Node4) * nodes.size(), hipMemcpyHostToDevice));
     GI_TRY_HIP(c, hipMemcpy(c->d_tris, tris.data(), sizeof(float4) * tris.size(), hipMemcpyHostToDevice));
     GI_TRY_HIP(c, hipMemcpy(c->d_tnrm, tn.data(), sizeof(float4) * tn.size(), hipMemcpyHostToDevice));
@@ -629,16 +634,25 @@ gi_status gi_set_dynamic_triangles(gi_context* c, const float* h_tv, const uint3
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     for (uint32_t k = 0; k < n; ++k)
       if (h_mat[k] >= c->n_mats) return fail(c, GI_ERR_INVALID_ARG, "material index out of range");
-    std::vector<float4> tv(3 * (size_t)std::max(n, 1u));
+    // the box of all of them, then their vertices; and their normals
+    std::vector<float4> tv(2 + 3 * (size_t)n);
     std::vector<float4> tn(std::max(n, 1u));
+    float lo[3] = {3.0e38f, 3.0e38f, 3.0e38f}, hi[3] = {-3.0e38f, -3.0e38f, -3.0e38f};
+    for (uint32_t k = 0; k < 3 * n; ++k)
+      for (int a = 0; a < 3; ++a) {
+        lo[a] = std::min(lo[a], h_tv[3 * (size_t)k + a]);
+        hi[a] = std::max(hi[a], h_tv[3 * (size_t)k + a]);
+      }
+    tv[0] = make_float4(lo[0], lo[1], lo[2], 0.0f);
+    tv[1] = make_float4(hi[0], hi[1], hi[2], 0.0f);
     for (uint32_t k = 0; k < n; ++k) {
       const float* v = h_tv + 9 * (size_t)k;
       uint32_t id = c->nt + k;
       float w;
       std::memcpy(&w, &id, 4);
-      tv[3 * k] = make_float4(v[0], v[1], v[2], w);
-      tv[3 * k + 1] = make_float4(v[3], v[4], v[5], 0.0f);
-      tv[3 * k + 2] = make_float4(v[6], v[7], v[8], 0.0f);
+      tv[2 + 3 * k] = make_float4(v[0], v[1], v[2], w);
+      tv[3 + 3 * k] = make_float4(v[3], v[4], v[5], 0.0f);
+      tv[4 + 3 * k] = make_float4(v[6], v[7], v[8], 0.0f);
       float nn[3];
       unit_normal(v, nn);
       uint32_t mb = h_mat[k];
@@ -647,13 +661,13 @@ gi_status gi_set_dynamic_triangles(gi_context* c, const float* h_tv, const uint3
     }
     if (n) {
       int slot;
-      char* st = stage_acquire(c, sizeof(float4) * 4 * n, &slot);
+      const size_t tvb = sizeof(float4) * tv.size();
+      char* st = stage_acquire(c, tvb + sizeof(float4) * n, &slot);
       if (!st) return fail(c, GI_ERR_OOM, "pinned staging allocation failed");
-      std::memcpy(st, tv.data(), sizeof(float4) * 3 * n);
-      std::memcpy(st + sizeof(float4) * 3 * n, tn.data(), sizeof(float4) * n);
-      GI_TRY_HIP(c, hipMemcpyAsync(c->d_dyn, st, sizeof(float4) * 3 * n, hipMemcpyHostToDevice, s));
-      GI_TRY_HIP(c, hipMemcpyAsync(c->d_tnrm + c->nt, st + sizeof(float4) * 3 * n, sizeof(float4) * n,
-                                   hipMemcpyHostToDevice, s));
+      std::memcpy(st, tv.data(), tvb);
+      std::memcpy(st + tvb, tn.data(), sizeof(float4) * n);
+      GI_TRY_HIP(c, hipMemcpyAsync(c->d_dyn, st, tvb, hipMemcpyHostToDevice, s));
+      GI_TRY_HIP(c, hipMemcpyAsync(c->d_tnrm + c->nt, st + tvb, sizeof(float4) * n, hipMemcpyHostToDevice, s));
       stage_release(c, slot, s);
     }
     const gi_status st = upload_emitters(c, h_tv, h_mat, n, s);

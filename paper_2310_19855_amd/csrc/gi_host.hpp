@@ -63,7 +63,7 @@ struct gi_context {
   float4* d_tris = nullptr;     // leaf-ordered triangles, 3 float4 each (v0.w = index)
   float4* d_tnrm = nullptr;     // [nt + kMaxDyn] unit normal, w = material index
   float4* d_mats = nullptr;     // [2 * n_mats]: albedo, emission
-  float4* d_dyn = nullptr;      // [3 * kMaxDyn]
+  float4* d_dyn = nullptr;      // box corners [2], then [3 * kMaxDyn] vertices of the dynamic triangles
   uint32_t n_dyn = 0;
   uint32_t* d_etri = nullptr;   // emitter triangles
   uint32_t* d_ethr = nullptr;   // their cumulative-area thresholds (scaled to 2^32)

@@ -20,6 +20,7 @@ constexpr uint32_t kLeafCountShift = 24;
 constexpr uint32_t kLeafCountMask = 0x7Fu;        // count - 1 in 7 bits (<= 128 triangles)
 constexpr uint32_t kLeafFirstMask = 0x00FFFFFFu;  // first triangle < 2^24
 constexpr uint32_t kNodeEmpty = 0xFFFFFFFFu;
+constexpr uint32_t kLeafMaxTris = 2;               // triangles per leaf that the builder makes
 
 constexpr uint32_t kBucketSlots = 32;   // world-cache slots per bucket (one 128-byte line of fingerprints)
 constexpr uint32_t kStatStripesHost = 64;   // copies of the stats counters (and hit-list stripes)
