@@ -14,6 +14,7 @@ if not torch.cuda.is_available():
 import oracle as O  # noqa: E402
 from paper_2310_19855_amd import gi  # noqa: E402
 from paper_2310_19855_amd import inputs as I  # noqa: E402
+from test_gpu_parity import _run_stage_parity  # noqa: E402
 
 
 def _layers():
@@ -92,3 +93,10 @@ def test_walks_equal_brute_force(kind):
     o4[:, 3] = tm
     ctx.trace_rays(torch.from_numpy(o4).cuda(), torch.from_numpy(d4).cuda(), tri, t, any_hit=True)
     assert np.array_equal(tri.cpu().numpy().view(np.uint32), osc.any(o, d, tm))
+
+
+@pytest.mark.parametrize("width,height,rays", [(8, 8, 1), (488, 8, 64), (488, 16, 64), (976, 8, 63)])
+def test_every_block_of_probe_rays_is_traced(width, height, rays):
+    """block counts of 1, 61 and 122 (multiples of the smallest block order) and one with a part of
+    a block at the end: every ray record and cell sum against the oracle"""
+    _run_stage_parity(I.room_scene(), dict(width=width, height=height, rays_per_probe=rays, table_log2=16), [0, 1])
