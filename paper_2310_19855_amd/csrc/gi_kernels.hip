@@ -1206,13 +1206,20 @@ __global__ __launch_bounds__(kTraceBlock) void k_shade_hits(SceneView sv, ShadeT
     g2 += qv[3 * i + 2];
   }
   if ((uint32_t)__ffsll((long long)same) - 1u == (threadIdx.x & 63u)) {
-    uint32_t* accp = reinterpret_cast<uint32_t*>(c.acc + slot);
-    const uint32_t o0 = atomicAdd(accp + 0, g0);
-    const uint32_t o1 = atomicAdd(accp + 1, g1);
-    const uint32_t o2 = atomicAdd(accp + 2, g2);
-    atomicAdd(accp + 3, (uint32_t)__popcll(same));
-    const uint32_t wraps = (o0 + g0 < o0) + (o1 + g1 < o1) + (o2 + g2 < o2);
-    if (wraps) atomicAdd(&stats[GI_STAT_WRAPS], (unsigned long long)wraps);
+    // two 64-bit atomics (r | g << 32, b | count << 32) instead of four 32-bit ones: the pass is
+    // bound by the rate of its atomics where many cells are hit (4K field, 485 -> 408 us; 480x270
+    // room with bounces 61 -> 52; 64 lights at 1281x717 293 -> 263; field at 1080 170 -> 161).  A low word that wraps carries one
+    // into the high word; the lane whose addition wrapped it takes that one back, so the four
+    // sums end as if added apart, and the high words' wraps count net of it
+    unsigned long long* accp = reinterpret_cast<unsigned long long*>(c.acc + slot);
+    const unsigned long long a0 = (unsigned long long)g0 | ((unsigned long long)g1 << 32);
+    const unsigned long long a1 = (unsigned long long)g2 | ((unsigned long long)__popcll(same) << 32);
+    const unsigned long long o0 = atomicAdd(accp, a0), o1 = atomicAdd(accp + 1, a1);
+    const bool w0 = (uint32_t)o0 + g0 < g0, w2 = (uint32_t)o1 + g2 < g2;
+    int wraps = (w0 ? 1 : 0) + (w2 ? 1 : 0) + (o0 + a0 < o0 ? 1 : 0);
+    if (w0 && atomicAdd(accp, 0xFFFFFFFF00000000ull) < 0x100000000ull) --wraps;
+    if (w2) atomicAdd(accp + 1, 0xFFFFFFFF00000000ull);
+    if (wraps) atomicAdd(&stats[GI_STAT_WRAPS], (unsigned long long)(long long)wraps);
   }
 }
 
