@@ -429,7 +429,7 @@ gi_status gi_create(const gi_config* cfg, gi_context** out) {
     c->hit_blocks_per_stripe = (nblk + gi::kStatStripesHost - 1) / gi::kStatStripesHost;
     c->hit_stripe_cap = c->hit_blocks_per_stripe * 64;
     A(dalloc(&c->d_hit_ids, (size_t)c->hit_stripe_cap * gi::kStatStripesHost));
-    A(dalloc(&c->d_hit_count, gi::kStatStripesHost));
+    A(dalloc(&c->d_hit_count, gi::kStatStripesHost * gi::kHitCountStride));
   }
   A(dalloc(&c->d_moments, 640));
   if (e == hipSuccess) {
@@ -444,7 +444,7 @@ gi_status gi_create(const gi_config* cfg, gi_context** out) {
     A(hipMemset(c->tab.meta, 0, 8 * (size_t)c->N));
     A(hipMemset(c->tab.accessed, 0, 4 * (size_t)c->N));
     A(hipMemset(c->d_stats, 0, 8 * (size_t)GI_STAT_COUNT * gi::kStatStripesHost));
-    A(hipMemset(c->d_hit_count, 0, 4 * gi::kStatStripesHost));
+    A(hipMemset(c->d_hit_count, 0, 4 * gi::kStatStripesHost * gi::kHitCountStride));
     A(hipMemset(c->d_rec, 0, 16 * PR));
     A(hipMemset(c->d_rkey, 0, 8 * PR));
     A(hipMemset(c->d_atlas, 0, 16 * (size_t)c->P * 64));

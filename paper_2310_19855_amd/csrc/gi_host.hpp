@@ -131,7 +131,7 @@ struct gi_context {
   gi::Table tab;
   unsigned long long* d_stats = nullptr;  // [kStatStripes][GI_STAT_COUNT]
   uint32_t* d_hit_ids = nullptr;          // compacted hit list, kStatStripes stripes
-  uint32_t* d_hit_count = nullptr;        // [kStatStripes]
+  uint32_t* d_hit_count = nullptr;        // [kStatStripes], kHitCountStride words apart
   uint32_t hit_blocks_per_stripe = 0, hit_stripe_cap = 0;
   float* d_moments = nullptr;   // [64*10]
   // learned

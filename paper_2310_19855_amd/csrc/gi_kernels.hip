@@ -4,7 +4,6 @@
 
 #include <cstring>
 #include <mutex>
-#include <numeric>
 
 #include "gi_device.hpp"
 #include "gi_host.hpp"
@@ -274,7 +273,7 @@ __global__ __launch_bounds__(256) void k_spawn_mips(const float4* gpos, const fl
     stats[t * GI_STAT_COUNT + GI_STAT_LIVE] = 0;
     stats[t * GI_STAT_COUNT + GI_STAT_RELAXED] = 0;
     stats[t * GI_STAT_COUNT + GI_STAT_NOPROBE] = 0;
-    hit_count[t] = 0;
+    hit_count[t * kHitCountStride] = 0;
   }
   const uint32_t tx = blockIdx.x * 16u + (t & 15u), ty = blockIdx.y * 16u + (t >> 4);
   uint32_t m = kSentinel;
@@ -495,31 +494,27 @@ __device__ inline void probe_ray(const ProbeRayArgs& a, uint32_t gid, uint32_t p
 }
 
 // Hits are regrouped for the shading pass: each wave ballots its hit lanes and appends their
-// ray ids to the list stripe of its 64 rays' range with one atomic per wave, so the shading
+// ray ids to the list stripe of its block range with one atomic per wave, so the shading
 // waves run dense.  The list order is not deterministic; nothing downstream depends on it
-// (cell sums are integer and the cell map is order-free).
-// The stripes are contiguous ranges of rays, for the shading's locality; block b traces the 64
-// rays of place (b * order) mod blocks, with order coprime to the number of blocks, so that the
-// waves in flight together append to all 64 counters (one atomic on one address takes about
-// 5 ns, and in ray order they all met at one or two) and hold cheap and costly regions side by
-// side.  Probe rays of the field: 1920x1080 298 -> 282 us, 3840x2160 870 -> 606 us, of a room at
-// 1281x717 with 32 rays 78 -> 66 us; order 12,289 and groups of 8 or 64 neighbouring blocks
-// measured the same within 3 %.
+// (cell sums are integer and the cell map is order-free).  Each stripe's counter has a cache
+// line of its own: atomics to one line pass one at a time (about 5 ns each), whatever words of
+// it they hit, and with the 64 counters in two lines the appends of a 4K frame's waves took
+// 265 of the trace's 870 us (field: 4K 870 -> 604 us, 1080p 298 -> 276; room at 1281x717 with 32
+// rays 78 -> 53).
 struct HitList {
   uint32_t* ids;          // [kStatStripes * stripe_cap]
-  uint32_t* count;        // [kStatStripes]
+  uint32_t* count;        // [kStatStripes], kHitCountStride words apart
   uint32_t stripe_cap;    // ray slots per stripe (= blocks per stripe * 64)
   uint32_t blocks_per_stripe;
 };
 
 template <int STACK>
 __global__ __launch_bounds__(kTraceBlock) void k_trace_probes(SceneView sv, ShadeTables st, ProbeRayArgs a,
-                                                              uint4* rec, uint2* rkey, HitList hl, uint32_t order,
+                                                              uint4* rec, uint2* rkey, HitList hl,
                                                               unsigned long long* stats) {
   __shared__ uint32_t stk[STACK * kTraceBlock];
   __shared__ uint16_t stkt[STACK * kTraceBlock];
-  const uint32_t place = (blockIdx.x * order) % gridDim.x;
-  const uint32_t gid = place * kTraceBlock + threadIdx.x;
+  const uint32_t gid = blockIdx.x * kTraceBlock + threadIdx.x;
   if (gid >= a.P * a.R) return;
   TStack<STACK, kTraceBlock> ts(stk + threadIdx.x, stkt + threadIdx.x, sv.spill + gid, sv.spill_stride);
   const uint32_t p = gid / a.R;
@@ -555,10 +550,10 @@ __global__ __launch_bounds__(kTraceBlock) void k_trace_probes(SceneView sv, Shad
   }
   const uint64_t m = __ballot(hit);
   if (m) {
-    const uint32_t stripe = place / hl.blocks_per_stripe;
+    const uint32_t stripe = blockIdx.x / hl.blocks_per_stripe;
     const uint32_t leader = (uint32_t)__ffsll((long long)__ballot(1)) - 1u;
     uint32_t base = 0;
-    if ((threadIdx.x & 63u) == leader) base = atomicAdd(&hl.count[stripe], (uint32_t)__popcll(m));
+    if ((threadIdx.x & 63u) == leader) base = atomicAdd(&hl.count[stripe * kHitCountStride], (uint32_t)__popcll(m));
     base = __shfl(base, (int)leader, 64);
     if (hit) hl.ids[stripe * hl.stripe_cap + base + (uint32_t)__popcll(m & lanes_below())] = gid;
   }
@@ -1060,7 +1055,7 @@ __global__ __launch_bounds__(kTraceBlock) void k_shade_hits(SceneView sv, ShadeT
   // block b shades items [w * 64, w * 64 + 64) of list stripe b / blocks_per_stripe
   const uint32_t stripe = blockIdx.x / hl.blocks_per_stripe;
   const uint32_t item = (blockIdx.x % hl.blocks_per_stripe) * kTraceBlock + threadIdx.x;
-  if (stripe >= kStatStripes || item >= hl.count[stripe]) return;
+  if (stripe >= kStatStripes || item >= hl.count[stripe * kHitCountStride]) return;
   const uint32_t gid = hl.ids[stripe * hl.stripe_cap + item];
   TStack<STACK, kTraceBlock> ts(stk + threadIdx.x, stkt + threadIdx.x, sv.spill + gid, sv.spill_stride);
   const uint4 rr = rec[gid];
@@ -2320,14 +2315,6 @@ hipError_t launch_spawn(gi_context* c, const float4* pos, const float4* nrm, con
   return hipGetLastError();
 }
 
-// the smallest number from 61 on that is coprime to the number of blocks (at most 2^22, so
-// that block * order stays below 2^32)
-static uint32_t trace_order(uint32_t nblocks) {
-  uint32_t m = 61u;
-  while (std::gcd(m, nblocks) != 1u) ++m;
-  return m;
-}
-
 hipError_t launch_trace(gi_context* c, hipStream_t s) {
   const uint64_t n = (uint64_t)c->P * c->R;
   const SceneView sv = scene_view(c);
@@ -2336,7 +2323,7 @@ hipError_t launch_trace(gi_context* c, hipStream_t s) {
   const CacheArgs ca = cache_args(c);
   const LearnedShadeOut lso = learned_shade_out(c);
   if (lso.tflag) k_zero_u32<<<blocks(lso.tflag_words, 256), 256, 0, s>>>(reinterpret_cast<uint32_t*>(lso.tflag), lso.tflag_words);
-  GI_TIMED(c, "trace_probes", s, (k_trace_probes<kLdsStack><<<blocks(n, kTraceBlock), kTraceBlock, 0, s>>>(sv, st, a, c->d_rec, c->d_rkey, hit_list(c), trace_order(blocks(n, kTraceBlock)), c->d_stats)));
+  GI_TIMED(c, "trace_probes", s, (k_trace_probes<kLdsStack><<<blocks(n, kTraceBlock), kTraceBlock, 0, s>>>(sv, st, a, c->d_rec, c->d_rkey, hit_list(c), c->d_stats)));
   const RestirArgs ra = restir_args(c);
   if (ra.on) {
     const uint32_t NR = 1u << c->cfg.restir_log2;

@@ -1210,7 +1210,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 8))) void
   if (HITLIST) {
     const uint32_t stripe = blockIdx.x / blocks_per_stripe;
     item = (blockIdx.x % blocks_per_stripe) * 64u + lane;
-    valid = stripe < kStatStripes && item < list_count[stripe];
+    valid = stripe < kStatStripes && item < list_count[stripe * kHitCountStride];
     oidx = valid ? list_ids[stripe * stripe_cap + item] : 0u;
   } else {
     item = blockIdx.x * 64u + lane;
@@ -1354,7 +1354,7 @@ __global__ void k_judge(const uint32_t* ids, const uint32_t* count, uint32_t str
   const uint32_t stripe = blockIdx.x / blocks_per_stripe;
   const uint32_t item = (blockIdx.x % blocks_per_stripe) * blockDim.x + threadIdx.x;
   float dn = 0.f, dd = 0.f;
-  if (stripe < kStatStripes && item < count[stripe]) {
+  if (stripe < kStatStripes && item < count[stripe * kHitCountStride]) {
     const uint32_t gid = ids[stripe * stripe_cap + item];
     const int32_t slot = (int32_t)rec[gid].x;
     if (slot >= 0 && meta[slot].x >= 64u) {

@@ -24,6 +24,7 @@ constexpr uint32_t kLeafMaxTris = 2;               // triangles per leaf that th
 
 constexpr uint32_t kBucketSlots = 32;   // world-cache slots per bucket (one 128-byte line of fingerprints)
 constexpr uint32_t kStatStripesHost = 64;   // copies of the stats counters (and hit-list stripes)
+constexpr uint32_t kHitCountStride = 32;    // words from one stripe's hit counter to the next: a 128-byte line each
 constexpr int kMaxDyn = 64;
 constexpr int kLdsStackEntries = 16;           // traversal-stack entries per lane kept in LDS
 constexpr int kNumCells = 64;

@@ -97,6 +97,6 @@ def test_walks_equal_brute_force(kind):
 
 @pytest.mark.parametrize("width,height,rays", [(8, 8, 1), (488, 8, 64), (488, 16, 64), (976, 8, 63)])
 def test_every_block_of_probe_rays_is_traced(width, height, rays):
-    """block counts of 1, 61 and 122 (multiples of the smallest block order) and one with a part of
-    a block at the end: every ray record and cell sum against the oracle"""
+    """1, 61 and 122 blocks of rays (fewer, about as many and more than the hit list's stripes) and
+    a part of a block at the end: every ray record and cell sum against the oracle"""
     _run_stage_parity(I.room_scene(), dict(width=width, height=height, rays_per_probe=rays, table_log2=16), [0, 1])
