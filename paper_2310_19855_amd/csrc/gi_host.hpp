@@ -160,6 +160,15 @@ namespace gi {
 void timer_begin(gi_context* c, const char* name, hipStream_t s, hipEvent_t* a);
 void timer_end(gi_context* c, const char* name, hipStream_t s, hipEvent_t a);
 
+// words[0] words of src to dst[0], the next words[1] to dst[1], ... in one launch
+struct UploadArgs {
+  static constexpr uint32_t kMax = 5;
+  const uint32_t* src;
+  uint32_t* dst[kMax];
+  uint32_t words[kMax];
+  uint32_t n;
+};
+hipError_t launch_upload(const UploadArgs& a, uint32_t total_words, hipStream_t s);
 hipError_t launch_gbuffer(gi_context* c, const gi_frame* f, float4* pos, float4* nrm, float4* alb,
                           uint32_t* prim, hipStream_t s);
 hipError_t launch_spawn(gi_context* c, const float4* pos, const float4* nrm, const uint32_t* prim, hipStream_t s);

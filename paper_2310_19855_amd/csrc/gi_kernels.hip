@@ -2087,6 +2087,17 @@ __global__ void k_zero_u64(unsigned long long* p, uint32_t n) {
   if (i < n) p[i] = 0ull;
 }
 
+__global__ __launch_bounds__(256) void k_upload(UploadArgs a, uint32_t total) {
+  const uint32_t i = blockIdx.x * 256u + threadIdx.x;
+  if (i >= total) return;
+  uint32_t at = 0;
+#pragma unroll
+  for (uint32_t k = 0; k < UploadArgs::kMax; ++k) {
+    if (k < a.n && i >= at && i < at + a.words[k]) a.dst[k][i - at] = a.src[i];
+    at += a.words[k];
+  }
+}
+
 // ------------------------------------------------------------------------------------------
 // launchers
 // ------------------------------------------------------------------------------------------
@@ -2242,6 +2253,11 @@ void timer_end(gi_context* c, const char* name, hipStream_t s, hipEvent_t a) {
   } while (0)
 
 static inline uint32_t blocks(uint64_t n, uint32_t b) { return (uint32_t)((n + b - 1) / b); }
+
+hipError_t launch_upload(const UploadArgs& a, uint32_t total_words, hipStream_t s) {
+  k_upload<<<blocks(total_words, 256), 256, 0, s>>>(a, total_words);
+  return hipGetLastError();
+}
 
 hipError_t launch_gbuffer(gi_context* c, const gi_frame* f, float4* pos, float4* nrm, float4* alb, uint32_t* prim,
                           hipStream_t s) {
