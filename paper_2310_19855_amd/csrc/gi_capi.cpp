@@ -767,12 +767,7 @@ gi_status gi_cache_update(gi_context* c, const gi_frame* f, void* stream) {
   GI_TRY_HIP(c, gi::launch_update(c, s));
   if (c->cfg.temporal) {
     // this frame's final probes become the history of the next one
-    GI_TRY_HIP(c, hipMemcpyAsync(c->d_prev_mask, c->d_mask, 4 * (size_t)c->P, hipMemcpyDeviceToDevice, s));
-    GI_TRY_HIP(c, hipMemcpyAsync(c->d_prev_pos, c->d_ppos, 16 * (size_t)c->P, hipMemcpyDeviceToDevice, s));
-    GI_TRY_HIP(c, hipMemcpyAsync(c->d_prev_nrm, c->d_pnrm, 16 * (size_t)c->P, hipMemcpyDeviceToDevice, s));
-    GI_TRY_HIP(c, hipMemcpyAsync(c->d_prev_atlas, c->d_atlas, 16 * 64 * (size_t)c->P, hipMemcpyDeviceToDevice, s));
-    if (c->d_prev_sh)
-      GI_TRY_HIP(c, hipMemcpyAsync(c->d_prev_sh, c->d_sh, 4 * 28 * (size_t)c->P, hipMemcpyDeviceToDevice, s));
+    GI_TRY_HIP(c, gi::launch_keep_probes(c, s));
     c->prev_frame = *f;
     c->has_prev = true;
   }

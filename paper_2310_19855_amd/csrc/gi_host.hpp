@@ -174,6 +174,7 @@ hipError_t launch_gbuffer(gi_context* c, const gi_frame* f, float4* pos, float4*
 hipError_t launch_spawn(gi_context* c, const float4* pos, const float4* nrm, const uint32_t* prim, hipStream_t s);
 hipError_t launch_trace(gi_context* c, hipStream_t s);
 hipError_t launch_update(gi_context* c, hipStream_t s);
+hipError_t launch_keep_probes(gi_context* c, hipStream_t s);
 hipError_t launch_interpolate(gi_context* c, const float4* pos, const float4* nrm, const uint32_t* prim,
                               float4* out, hipStream_t s);
 hipError_t launch_query(gi_context* c, const float4* pos, const float4* nrm, uint32_t n, float4* out,
