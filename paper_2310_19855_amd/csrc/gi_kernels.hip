@@ -1904,7 +1904,11 @@ __global__ __launch_bounds__(64 * WAVES) void k_interpolate(const float4* gpos, 
 // 2x2, 1x1 of the 8 tiles as sample-weighted means of their 2x2 children (children in raster
 // order).  Phase 3: each cell's radiance for readers from the finest of its level and its
 // parents that holds at least tile_min samples, else the coarsest level if it holds any, else
-// zero.  Every thread reaches every barrier; empty and evicted tiles skip the work.
+// zero.  Bound by HBM streaming, so only what can change is read: a tile that nothing accessed
+// has empty sums and keeps its radiance, samples and levels (its life alone is touched), one
+// whose accesses were lookups writes nothing, and in the others the cells without samples are
+// read for the levels but not written (1080p field with 2x2 upscaling: 67 -> 56 us).
+// Threads leave together or reach every barrier.
 // ------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(512) void k_cache_update_tiles(uint32_t* fp, uint64_t* key, uint4* acc, float4* L,
                                                             uint32_t* cn, float4* Lq, uint2* meta, uint32_t* accessed,
@@ -1912,24 +1916,52 @@ __global__ __launch_bounds__(512) void k_cache_update_tiles(uint32_t* fp, uint64
                                                             uint32_t tile_min, unsigned long long* stats) {
   __shared__ float lv[8][85][3];   // per tile: level 0 at 0..63, 1 at 64..79, 2 at 80..83, 3 at 84
   __shared__ uint32_t nv[8][85];
-  __shared__ uint32_t keep_s[8], live_s[8], life_s[8];
+  __shared__ uint32_t state_s[8], sum_s[8];   // per tile: kTile*, any sample this frame
   const uint32_t t = threadIdx.x, w = t >> 6, l = t & 63u;
   const uint32_t j = l & 7u, cell = 8u * w + (l >> 3);
   const uint32_t N = gridDim.x * 8u;
   const uint32_t s = blockIdx.x * 8u + j;
   const size_t e = (size_t)cell * N + s;
-  // the tile's state, read once before the thread of cell 0 rewrites it
+  // the tiles' state, read and rewritten by eight threads; a tile that nothing accessed this
+  // frame only grows older
+  enum : uint32_t { kTileIdle = 0, kTileTouched = 1, kTileEvicted = 2 };
+  uint32_t live = 0, state = kTileIdle;
   if (t < 8u) {
     const uint32_t st = blockIdx.x * 8u + t;
-    keep_s[t] = 0u;
-    live_s[t] = fp[st] != 0u;
-    life_s[t] = live_s[t] ? (accessed[st] ? max_life : meta[st].y - 1u) : 0u;
+    live = fp[st] != 0u;
+    const uint32_t acc_bit = accessed[st];
+    const uint32_t life = acc_bit ? max_life : meta[st].y - 1u;
+    if (live) {
+      state = life == 0u ? kTileEvicted : (acc_bit ? kTileTouched : kTileIdle);
+      meta[st] = make_uint2(0u, life);
+      if (acc_bit) accessed[st] = 0u;
+      if (state == kTileEvicted) {
+        fp[st] = 0u;
+        key[st] = 0u;
+      }
+      unsigned long long* sc = stats + (st % kStatStripes) * GI_STAT_COUNT;
+      atomicAdd(&sc[state == kTileEvicted ? GI_STAT_EVICT : GI_STAT_LIVE], 1ull);
+    }
+    state_s[t] = state;
+    sum_s[t] = 0u;
+  }
+  if (__syncthreads_count(state != kTileIdle) == 0) return;
+  const uint32_t mine = state_s[j];
+  uint4 a = make_uint4(0u, 0u, 0u, 0u);
+  float4 lc = make_float4(0.f, 0.f, 0.f, 0.f);
+  uint32_t nh = 0u;
+  if (mine == kTileTouched) {
+    a = acc[e];
+    lc = L[e];
+    nh = cn[e];
+    if (a.w > 0u) sum_s[j] = 1u;
+  } else if (mine == kTileEvicted) {
+    L[e] = make_float4(0.f, 0.f, 0.f, 0.f);
+    cn[e] = 0u;
+    Lq[e] = make_float4(0.f, 0.f, 0.f, 0.f);
   }
   __syncthreads();
-  if (live_s[j]) {
-    const uint4 a = acc[e];
-    float4 lc = L[e];
-    uint32_t nh = cn[e];
+  if (sum_s[j]) {
     if (a.w > 0u) {
       const uint32_t h = nh < n_cap ? nh : n_cap;
       const float wt = (float)a.w / (float)((double)h + (double)a.w);
@@ -1942,35 +1974,14 @@ __global__ __launch_bounds__(512) void k_cache_update_tiles(uint32_t* fp, uint64
       lc.z = lc.z + wt * (m2 - lc.z);
       const uint64_t u = (uint64_t)nh + a.w;
       nh = u < n_cap ? (uint32_t)u : n_cap;
-    }
-    acc[e] = make_uint4(0u, 0u, 0u, 0u);
-    const uint32_t life = life_s[j];
-    unsigned long long* st = stats + (s % kStatStripes) * GI_STAT_COUNT;
-    if (life == 0u) {
-      L[e] = make_float4(0.f, 0.f, 0.f, 0.f);
-      cn[e] = 0u;
-      Lq[e] = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (cell == 0u) {
-        fp[s] = 0u;
-        key[s] = 0u;
-        meta[s] = make_uint2(0u, 0u);
-        accessed[s] = 0u;
-        atomicAdd(&st[GI_STAT_EVICT], 1ull);
-      }
-    } else {
+      acc[e] = make_uint4(0u, 0u, 0u, 0u);
       L[e] = lc;
       cn[e] = nh;
-      if (cell == 0u) {
-        meta[s] = make_uint2(0u, life);
-        accessed[s] = 0u;
-        keep_s[j] = 1u;
-        atomicAdd(&st[GI_STAT_LIVE], 1ull);
-      }
-      lv[j][cell][0] = lc.x;
-      lv[j][cell][1] = lc.y;
-      lv[j][cell][2] = lc.z;
-      nv[j][cell] = nh;
     }
+    lv[j][cell][0] = lc.x;
+    lv[j][cell][1] = lc.y;
+    lv[j][cell][2] = lc.z;
+    nv[j][cell] = nh;
   }
   __syncthreads();
   // level k + 1 (side 8 >> (k+1), 8 tiles x side^2 entries) from level k (side 8 >> k)
@@ -1980,7 +1991,7 @@ __global__ __launch_bounds__(512) void k_cache_update_tiles(uint32_t* fp, uint64
     const uint32_t side = 8u >> (k + 1u), per = side * side;
     if (t < 8u * per) {
       const uint32_t tj = t / per, i = t % per;
-      if (keep_s[tj]) {
+      if (sum_s[tj]) {
         const uint32_t x = i % side, y = i / side;
         float w0 = 0.f, w1 = 0.f, w2 = 0.f;
         uint32_t ns = 0u;
@@ -2002,7 +2013,7 @@ __global__ __launch_bounds__(512) void k_cache_update_tiles(uint32_t* fp, uint64
     }
     __syncthreads();
   }
-  if (!keep_s[j]) return;
+  if (!sum_s[j]) return;
   const uint32_t x = cell & 7u, y = cell >> 3;
   int32_t pick = -1;
 #pragma unroll
