@@ -261,9 +261,11 @@ void free_frame_buffers(gi_context* c) {
     dfree(c->d_rs_m[t]);
   }
   dfree(c->d_rs_claim);
+  dfree(c->d_rs_place);
   dfree(c->d_r_rs_yw);
   dfree(c->d_r_rs_n);
   dfree(c->d_r_rs_m);
+  dfree(c->d_r_rs_key);
   dfree(c->d_r_rs_slot);
   dfree(c->d_sh);
   dfree(c->tab.fp);
@@ -441,9 +443,11 @@ gi_status gi_create(const gi_config* cfg, gi_context** out) {
       A(dalloc(&c->d_rs_m[t], NR));
     }
     A(dalloc(&c->d_rs_claim, NR));
+    A(dalloc(&c->d_rs_place, gi::restir_places(cfg->restir_log2)));
     A(dalloc(&c->d_r_rs_yw, PR));
     A(dalloc(&c->d_r_rs_n, PR));
     A(dalloc(&c->d_r_rs_m, PR));
+    A(dalloc(&c->d_r_rs_key, PR));
     A(dalloc(&c->d_r_rs_slot, PR));
   }
   A(dalloc(&c->d_sh, (size_t)c->P * 28));

@@ -117,10 +117,12 @@ struct gi_context {
   float4* d_rs_yw[2] = {nullptr, nullptr};   // light point, contribution weight
   float4* d_rs_n[2] = {nullptr, nullptr};    // normal of the storing vertex, w = light bits
   uint32_t* d_rs_m[2] = {nullptr, nullptr};  // count
-  uint32_t* d_rs_claim = nullptr;            // lowest ray id offering to each slot
+  uint32_t* d_rs_claim = nullptr;            // lowest ray id bidding for each slot
+  uint32_t* d_rs_place = nullptr;            // [restir_places] lowest ray id per hash of the cell
   float4* d_r_rs_yw = nullptr;               // [P*R] each hit's final reservoir
   float4* d_r_rs_n = nullptr;
   uint32_t* d_r_rs_m = nullptr;              // 0: none
+  uint64_t* d_r_rs_key = nullptr;            // its cell
   int32_t* d_r_rs_slot = nullptr;
   uint32_t rs_cur = 0;                       // table read this frame
   bool rs_has_prev = false;
@@ -190,6 +192,8 @@ hipError_t launch_count_traversal(gi_context* c, unsigned long long* out, hipStr
 constexpr size_t kNoAllocScratchWords = (size_t)4 << 20;
 constexpr int kMaxDevices = 64;
 hipError_t scratch_init(int device);
+// places the rays of a reservoir cell bid for: sixteen per table slot, at most 2^22
+inline uint32_t restir_places(uint32_t restir_log2) { return 1u << (restir_log2 < 18u ? restir_log2 + 4u : 22u); }
 uint32_t noalloc_chunk_rays(uint32_t spill_rows);
 hipError_t launch_trace_rays_noalloc(gi_context* c, const float4* o, const float4* d, uint32_t n, uint32_t any,
                                      uint32_t* tri, float* t, hipStream_t s);

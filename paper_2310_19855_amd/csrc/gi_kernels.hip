@@ -2,6 +2,7 @@
 #include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstring>
 #include <mutex>
 
@@ -624,6 +625,19 @@ __device__ inline int32_t table_lookup(const CacheArgs& c, uint64_t key) {
   return r < 0 ? -1 : (int32_t)(b * kBucket) + r;
 }
 
+// a bucket's fingerprints as they are in memory, past the caches of this XCD (other XCDs' inserts
+// of this launch included): 16-byte buffer loads with the scope bit of a device-scope atomic load
+// (sc1, bit 4 of the cache policy).  Such loads pass at about the rate of atomics (20 G/s over
+// the chip, whatever their width), so a line is read in 8 of them, not 32
+__device__ inline __amdgpu_buffer_rsrc_t slots_buffer(const uint32_t* fp, uint32_t n_slots) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(fp), (short)0, (int)(n_slots * 4u), 0x00027000);
+}
+
+__device__ inline uint4 load_slots_coherent(__amdgpu_buffer_rsrc_t r, uint32_t first_slot) {
+  const auto x = __builtin_amdgcn_raw_buffer_load_b128(r, (int)(first_slot * 4u), 0, 16);
+  return make_uint4((uint32_t)x[0], (uint32_t)x[1], (uint32_t)x[2], (uint32_t)x[3]);
+}
+
 // find-or-insert: the fingerprint is searched in the whole bucket first; otherwise the first
 // empty slot is claimed with compare-and-swap.  Each round reads the bucket's fingerprints
 // with coherent loads issued together; a CAS that finds our own fingerprint means another
@@ -636,14 +650,19 @@ __device__ inline int32_t table_insert(const CacheArgs& c, uint64_t key, bool& i
   const uint32_t b = bucket_of(key, c.bucket_mask), f = fingerprint_of(key);
   uint32_t* line = c.fp + b * kBucket;
   for (uint32_t round = 0; round <= kBucket; ++round) {
-    uint32_t cur[kBucket];
+    const __amdgpu_buffer_rsrc_t r = slots_buffer(c.fp, (c.bucket_mask + 1u) * kBucket);
+    uint4 v[kBucket / 4];
 #pragma unroll
-    for (uint32_t s = 0; s < kBucket; ++s) cur[s] = __hip_atomic_load(line + s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    for (uint32_t q = 0; q < kBucket / 4u; ++q) v[q] = load_slots_coherent(r, b * kBucket + 4u * q);
     int32_t own = -1, empty = -1;
 #pragma unroll
-    for (int s = (int)kBucket - 1; s >= 0; --s) {
-      if (cur[s] == f) own = s;
-      if (cur[s] == 0u) empty = s;
+    for (int q = (int)kBucket / 4 - 1; q >= 0; --q) {
+      const uint32_t x[4] = {v[q].x, v[q].y, v[q].z, v[q].w};
+#pragma unroll
+      for (int k = 3; k >= 0; --k) {
+        if (x[k] == f) own = 4 * q + k;
+        if (x[k] == 0u) empty = 4 * q + k;
+      }
     }
     if (own >= 0) return (int32_t)(b * kBucket) + own;
     if (empty < 0) return -1;
@@ -654,6 +673,25 @@ __device__ inline int32_t table_insert(const CacheArgs& c, uint64_t key, bool& i
       return (int32_t)(b * kBucket) + empty;
     }
     if (prev == f) return (int32_t)(b * kBucket) + empty;
+  }
+  return -1;
+}
+
+// find-or-insert in a table that starts the launch empty (reservoirs): compare-and-swap from the
+// slot that the fingerprint names, on to the next one inside the bucket while another cell is
+// there.  No read goes before it, and cells of one bucket start at different slots, where all of
+// them claimed its first empty slot and all but one failed (38 -> 16 us for the claims of the pass below)
+__device__ inline int32_t table_insert_empty(const CacheArgs& c, uint64_t key, bool& inserted) {
+  const uint32_t first = bucket_of(key, c.bucket_mask) * kBucket, f = fingerprint_of(key);
+  inserted = false;
+  for (uint32_t k = 0; k < kBucket; ++k) {
+    const uint32_t s = first + ((f + k) & (kBucket - 1u));
+    const uint32_t prev = atomicCAS(c.fp + s, 0u, f);
+    if (prev == 0u) {
+      c.key[s] = key;
+      inserted = true;
+    }
+    if (prev == 0u || prev == f) return (int32_t)s;
   }
   return -1;
 }
@@ -747,11 +785,14 @@ struct RestirArgs {
   const float4* pyw;            // read table: light point, weight
   const float4* pn;             // read table: normal, w = light bits
   const uint32_t* pm;           // read table: count
-  uint32_t* claim;              // written table: lowest ray id per slot
+  uint32_t* claim;              // written table: lowest ray id bidding for the slot
+  uint32_t* place;              // lowest ray id per hash of the cell
+  uint32_t place_mask;
   float4* r_yw;                 // per ray: final reservoir
   float4* r_n;
-  uint32_t* r_m;
-  int32_t* r_slot;
+  uint32_t* r_m;                // 0: none
+  uint64_t* r_key;              // its cell
+  int32_t* r_slot;              // the slot it bids for, or -1
   float cell_scale, lod_scale, cam[3];
 };
 
@@ -862,21 +903,15 @@ __device__ inline LightSample sample_light_ris(const ShadeTables& st, const Rest
     }
   }
   if (k_sel == 0xFFFFFFFFu) {
-    if (ra.on) {
-      ra.r_m[gid] = 0u;
-      ra.r_slot[gid] = -1;
-    }
+    if (ra.on) ra.r_m[gid] = 0u;
     return ls;
   }
   const float W = wsum / ((float)M * ph_sel);
   if (ra.on) {
-    bool ins;
-    const int32_t slot = table_insert(ra.next, pkey, ins);
     ra.r_yw[gid] = make_float4(sx, sy, sz, W);
     ra.r_n[gid] = make_float4(nx, ny, nz, __uint_as_float(k_sel));
     ra.r_m[gid] = M;
-    ra.r_slot[gid] = slot;
-    if (slot >= 0) atomicMin(ra.claim + slot, gid);
+    ra.r_key[gid] = pkey;
   }
   ls.cast = true;
   ls.ray = make_ray(px, py, pz, ox, oy, oz);
@@ -1058,14 +1093,57 @@ __global__ __launch_bounds__(64) void k_light_grid(ShadeTables st, uint32_t n_em
   if (lane == 0u) count[ci] = cnt;
 }
 
-// World-space reservoirs (Section 2.3.1): the table written this frame starts empty; after
-// the shading, each slot takes the reservoir of the lowest ray id that offered to it.
-__global__ __launch_bounds__(256) void k_restir_clear(uint32_t* fp, uint64_t* key, uint32_t* claim, uint32_t n) {
+// World-space reservoirs (Section 2.3.1): the table written this frame starts empty; after the
+// shading, each cell takes the reservoir of the lowest ray id that offers to it.  A cell collects
+// dozens of rays, and where every one of them looks for its cell in the empty table at once they
+// fail each other's claims of a bucket's slots over and over (many-light room at 1281x717: 152 us of
+// the shading's 265 when every hit inserted, 137 in a pass of its own).  So the rays first
+// bid for a place by the hash of their cell alone, an atomic minimum with no search; the winner of
+// a place inserts its cell and stores (the lowest ray of a place is the lowest of its cell), and
+// the other rays of that cell are done.  Only the rays of a cell that lost its place to another
+// cell (one or two in a hundred: sixteen places per table slot) insert and bid for their slot.  Three
+// passes, 51 us together with the clearing.
+__global__ __launch_bounds__(256) void k_restir_clear(uint32_t* fp, uint64_t* key, uint32_t* claim, uint32_t n,
+                                                      uint32_t* place, uint32_t places) {
   const uint32_t i = blockIdx.x * 256u + threadIdx.x;
+  if (i < places) place[i] = 0xFFFFFFFFu;
   if (i >= n) return;
   fp[i] = 0u;
   key[i] = 0u;
   claim[i] = 0xFFFFFFFFu;
+}
+
+__device__ inline uint32_t restir_place(const RestirArgs& ra, uint64_t key) {
+  return hash_xxh32((uint32_t)key + hash_xxh32((uint32_t)(key >> 32))) & ra.place_mask;
+}
+
+__global__ __launch_bounds__(256) void k_restir_bid(const uint4* rec, uint32_t n, RestirArgs ra) {
+  const uint32_t gid = blockIdx.x * 256u + threadIdx.x;
+  if (gid >= n || !(rec[gid].w & GI_RAY_HIT) || ra.r_m[gid] == 0u) return;
+  uint32_t* p = ra.place + restir_place(ra, ra.r_key[gid]);
+  if (*p > gid) atomicMin(p, gid);     // bids only fall: a lower one, however old the read, settles it
+}
+
+__global__ __launch_bounds__(256) void k_restir_claim(const uint4* rec, uint32_t n, RestirArgs ra, float4* yw,
+                                                      float4* nrm, uint32_t* cnt) {
+  const uint32_t gid = blockIdx.x * 256u + threadIdx.x;
+  if (gid >= n || !(rec[gid].w & GI_RAY_HIT) || ra.r_m[gid] == 0u) return;
+  const uint64_t key = ra.r_key[gid];
+  const uint32_t w = ra.place[restir_place(ra, key)];
+  int32_t slot = -1;
+  bool inserted;
+  if (w == gid) {
+    const int32_t s = table_insert_empty(ra.next, key, inserted);
+    if (inserted) {       // else the bucket is full, or holds another cell of this fingerprint
+      yw[s] = ra.r_yw[gid];
+      nrm[s] = ra.r_n[gid];
+      cnt[s] = ra.r_m[gid];
+    }
+  } else if (ra.r_key[w] != key) {
+    slot = table_insert_empty(ra.next, key, inserted);
+    if (slot >= 0) atomicMin(ra.claim + slot, gid);
+  }
+  ra.r_slot[gid] = slot;
 }
 
 __global__ __launch_bounds__(256) void k_restir_store(const uint4* rec, uint32_t n, RestirArgs ra, float4* yw,
@@ -2268,9 +2346,12 @@ static RestirArgs restir_args(const gi_context* c) {
     r.pm = nullptr;
   }
   r.claim = c->d_rs_claim;
+  r.place = c->d_rs_place;
+  r.place_mask = restir_places(c->cfg.restir_log2) - 1u;
   r.r_yw = c->d_r_rs_yw;
   r.r_n = c->d_r_rs_n;
   r.r_m = c->d_r_rs_m;
+  r.r_key = c->d_r_rs_key;
   r.r_slot = c->d_r_rs_slot;
   r.cell_scale = c->cfg.cell_scale;
   r.lod_scale = c->cfg.lod_scale;
@@ -2407,7 +2488,7 @@ hipError_t launch_trace(gi_context* c, hipStream_t s) {
   const RestirArgs ra = restir_args(c);
   if (ra.on) {
     const uint32_t NR = 1u << c->cfg.restir_log2;
-    GI_TIMED(c, "restir_clear", s, (k_restir_clear<<<blocks(NR, 256), 256, 0, s>>>(ra.next.fp, ra.next.key, ra.claim, NR)));
+    GI_TIMED(c, "restir_clear", s, (k_restir_clear<<<blocks(std::max(NR, ra.place_mask + 1u), 256), 256, 0, s>>>(ra.next.fp, ra.next.key, ra.claim, NR, ra.place, ra.place_mask + 1u)));
   }
   if (c->cfg.light_grid) {
     // the light grid over this frame's hit points, before the shading that samples it
@@ -2421,7 +2502,10 @@ hipError_t launch_trace(gi_context* c, hipStream_t s) {
   if (ra.on) {
     // this frame's reservoirs into the written table (the lowest ray id per slot), which the
     // next frame reads
-    GI_TIMED(c, "restir_store", s, (k_restir_store<<<blocks(n, 256), 256, 0, s>>>(c->d_rec, (uint32_t)n, ra, c->d_rs_yw[c->rs_cur ^ 1u], c->d_rs_n[c->rs_cur ^ 1u], c->d_rs_m[c->rs_cur ^ 1u])));
+    const uint32_t nxt = c->rs_cur ^ 1u;
+    GI_TIMED(c, "restir_bid", s, (k_restir_bid<<<blocks(n, 256), 256, 0, s>>>(c->d_rec, (uint32_t)n, ra)));
+    GI_TIMED(c, "restir_claim", s, (k_restir_claim<<<blocks(n, 256), 256, 0, s>>>(c->d_rec, (uint32_t)n, ra, c->d_rs_yw[nxt], c->d_rs_n[nxt], c->d_rs_m[nxt])));
+    GI_TIMED(c, "restir_store", s, (k_restir_store<<<blocks(n, 256), 256, 0, s>>>(c->d_rec, (uint32_t)n, ra, c->d_rs_yw[nxt], c->d_rs_n[nxt], c->d_rs_m[nxt])));
     c->rs_cur ^= 1u;
     c->rs_has_prev = true;
   }
