@@ -80,6 +80,7 @@ struct LearnedState {
   uint32_t* tail_in = nullptr;   // whether that entry began inside the tile
   size_t n_pairs = 0;
   uint32_t key_bits = 0;         // bits of a gradient pair key (level * T + entry)
+  uint32_t entry_bits = 0;       // bits of its entry alone
   float* lpart = nullptr;        // [train_blocks] loss partials
   float2* judge_part = nullptr;  // per-wave (error, norm) partials of the judge
   uint32_t B = 0;
@@ -397,20 +398,21 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_hist(const uint32_t* key, uin
   if (threadIdx.x < 256u) hist[threadIdx.x * nb + blockIdx.x] = h[threadIdx.x];
 }
 
-// block d: exclusive prefix of digit d's block counts (in place) and the digit's total
-__global__ __launch_bounds__(256) void k_rs_digit_scan(uint32_t* hist, uint32_t nb, uint32_t* dtot) {
+// block (d, g): exclusive prefix of digit d's counts over the tiles of segment g (in place) and
+// the digit's total there
+__global__ __launch_bounds__(256) void k_rs_digit_scan(uint32_t* hist, uint32_t nb, uint32_t seg_tiles, uint32_t* dtot) {
   __shared__ uint32_t lds[4];
-  uint32_t* h = hist + (size_t)blockIdx.x * nb;
+  uint32_t* h = hist + (size_t)blockIdx.x * nb + (size_t)blockIdx.y * seg_tiles;
   uint32_t carry = 0u;
-  for (uint32_t c = 0; c < nb; c += 256u) {
+  for (uint32_t c = 0; c < seg_tiles; c += 256u) {
     const uint32_t i = c + threadIdx.x;
-    const uint32_t v = i < nb ? h[i] : 0u;
+    const uint32_t v = i < seg_tiles ? h[i] : 0u;
     uint32_t total;
     const uint32_t ex = block_excl_scan256(v, lds, total);
-    if (i < nb) h[i] = carry + ex;
+    if (i < seg_tiles) h[i] = carry + ex;
     carry += total;
   }
-  if (threadIdx.x == 0) dtot[blockIdx.x] = carry;
+  if (threadIdx.x == 0) dtot[256u * blockIdx.y + blockIdx.x] = carry;
 }
 
 // The tile is first ordered by digit in LDS, then written out so that consecutive threads
@@ -421,8 +423,8 @@ __global__ __launch_bounds__(256) void k_rs_digit_scan(uint32_t* hist, uint32_t 
 // order, and the digits' tile offsets place it.  Equal digits keep their input order.
 template <typename V>
 __global__ __launch_bounds__(kRsThreads) void k_rs_scatter(const uint32_t* kin, const V* vin, uint32_t* kout, V* vout,
-                                                           uint32_t n, uint32_t shift, uint32_t nb, const uint32_t* off,
-                                                           const uint32_t* dtot) {
+                                                           uint32_t n, uint32_t shift, uint32_t nb, uint32_t seg_tiles,
+                                                           const uint32_t* off, const uint32_t* dtot_all) {
   constexpr uint32_t W = kRsThreads / 64u, PW = kRsTile / W;
   static_assert(PW == 64u * kRsRounds && kRsThreads >= 256u, "a wave holds kRsRounds rounds of 64 items");
   __shared__ uint32_t sk[kRsTile];
@@ -434,6 +436,8 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_scatter(const uint32_t* kin, 
   const uint32_t t = threadIdx.x, lane = t & 63u, w = t >> 6;
   const uint32_t b0 = blockIdx.x * kRsTile;
   const uint32_t m = n - b0 < kRsTile ? n - b0 : kRsTile;     // items of this tile
+  const uint32_t seg = blockIdx.x / seg_tiles;                // sorted by itself
+  const uint32_t* dtot = dtot_all + 256u * seg;
   const uint64_t below = (1ull << lane) - 1ull;
   uint32_t key[kRsRounds], rk[kRsRounds];
   V val[kRsRounds];
@@ -495,7 +499,7 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_scatter(const uint32_t* kin, 
       e2 += ld[q];
     }
     lbase[t] = e1;
-    gbase[t] = e2 + off[t * nb + blockIdx.x];
+    gbase[t] = seg * seg_tiles * kRsTile + e2 + off[t * nb + blockIdx.x];
   }
   __syncthreads();
 #pragma unroll
@@ -523,19 +527,21 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_scatter(const uint32_t* kin, 
 
 // sorts (keys[0], vals[0]) by the low `bits` bits of the keys, stable; returns the index of
 // the buffer pair holding the result.  first_hist: the tile counts of the lowest digit are
-// already in hist (written with the keys)
+// already in hist (written with the keys).  segments > 1: so many equal runs of whole tiles are
+// sorted each by itself
 template <typename V>
 static hipError_t radix_sort(uint32_t* keys[2], V* vals[2], uint32_t n, uint32_t bits, uint32_t* hist,
-                             hipStream_t st, int& which, bool first_hist = false) {
+                             hipStream_t st, int& which, bool first_hist = false, uint32_t segments = 1) {
   which = 0;
   if (n == 0) return hipSuccess;
   const uint32_t nb = (n + kRsTile - 1u) / kRsTile;
+  const uint32_t seg_tiles = nb / segments;
   uint32_t* dtot = hist + 256u * nb;
   for (uint32_t shift = 0; shift < bits; shift += 8u) {
     if (shift > 0u || !first_hist) k_rs_hist<<<nb, kRsThreads, 0, st>>>(keys[which], n, shift, nb, hist);
-    k_rs_digit_scan<<<256, 256, 0, st>>>(hist, nb, dtot);
+    k_rs_digit_scan<<<dim3(256, segments), 256, 0, st>>>(hist, nb, seg_tiles, dtot);
     k_rs_scatter<V><<<nb, kRsThreads, 0, st>>>(keys[which], vals[which], keys[which ^ 1], vals[which ^ 1], n, shift, nb,
-                                               hist, dtot);
+                                               seg_tiles, hist, dtot);
     which ^= 1;
   }
   return hipGetLastError();
@@ -629,7 +635,8 @@ __device__ inline void atomic_max_abs(float* p, float v) {
 // pairs [256 L g, 256 L (g + 1)) in (level, sample, corner) order, so the pairs of one level,
 // which hold every copy of its keys, come in sample order across the groups.  When 256 L is a
 // whole number of sort tiles (L a multiple of 8) the block also counts the low key digits of
-// its tiles for the sort's first pass.
+// its tiles for the sort's first pass.  Or (by_level) in (level, group, sample, corner) order:
+// the levels are then sorted apart, by the entry alone; sorted, the two orders are the same.
 constexpr uint32_t kTrainWaves = 8;   // waves of a training block: one 16x16 tile of each layer's output each
 static_assert(64 * kTrainWaves == 32 * kMaxLevels, "one thread of a training block per (sample, level) of its group");
 
@@ -637,13 +644,13 @@ static_assert(64 * kTrainWaves == 32 * kMaxLevels, "one thread of a training blo
 __global__ __launch_bounds__(64 * kTrainWaves) __attribute__((amdgpu_waves_per_eu(4)))
 void k_train(LearnedParams lp, const float4* batch, uint32_t B, uint32_t off, uint32_t stride, const __half* grid_h,
              const __bf16* wb, float loss_scale, float* part, float* lpart, float* acc, float* amax, uint32_t log2T,
-             uint32_t* pkey, float2* pval, uint32_t nb, uint32_t* hist) {
+             uint32_t* pkey, float2* pval, uint32_t nb, uint32_t* hist, bool by_level) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   TrainSmem& S = *reinterpret_cast<TrainSmem*>(smem_raw);
   __shared__ float red[kTrainWaves][4];
   __shared__ uint32_t hs[2][256];       // low-digit counts of the group's sort tiles
   static_assert(kRsTile == 2048u && kMaxLevels <= 16, "a group's pairs are at most two sort tiles");
-  const bool tiles = (lp.L & 7u) == 0u;
+  const bool tiles = (lp.L & 7u) == 0u && !by_level;
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
   const __bf16* W1 = wb;
   const __bf16* W1t = wb + 4096;
@@ -845,7 +852,7 @@ void k_train(LearnedParams lp, const float4* batch, uint32_t B, uint32_t off, ui
         v[2 * c + 1] = cn.w[c] * d1;
         if (tiles) atomicAdd(&hs[l >> 3][k[c] & 255u], 1u);
       }
-      const size_t q = ((size_t)g * lp.L + (size_t)l) * 32u + (size_t)s;
+      const size_t q = (by_level ? (size_t)l * groups + g : (size_t)g * lp.L + (size_t)l) * 32u + (size_t)s;
       uint4* kq = reinterpret_cast<uint4*>(pkey + q * 8u);
       kq[0] = make_uint4(k[0], k[1], k[2], k[3]);
       kq[1] = make_uint4(k[4], k[5], k[6], k[7]);
@@ -1479,6 +1486,7 @@ hipError_t learned_create(gi_context* c) {
   uint32_t tbits = 0;
   while ((1u << tbits) < lp.T) ++tbits;
   s->key_bits = lbits + tbits;
+  s->entry_bits = tbits;
   for (int k = 0; k < 2; ++k) {
     A(lalloc(&s->bkeys[k], rows));
     A(lalloc(&s->bvals[k], rows));
@@ -1486,7 +1494,7 @@ hipError_t learned_create(gi_context* c) {
     A(lalloc(&s->pvals[k], s->n_pairs));
   }
   const size_t nb_max = (std::max(rows, s->n_pairs) + kRsTile - 1) / kRsTile;
-  A(lalloc(&s->rs_hist, 256 * nb_max + 256));
+  A(lalloc(&s->rs_hist, 256 * nb_max + 256 * kMaxLevels));
   const size_t ntiles = (s->n_pairs + kGredTile - 1) / kGredTile;
   A(lalloc(&s->tail_sum, ntiles));
   A(lalloc(&s->tail_in, ntiles));
@@ -1565,16 +1573,22 @@ static hipError_t train_step(gi_context* c, hipStream_t st, bool apply, uint32_t
   // gradient pairs fill [0, n_pairs) (L * B * 8)
   const uint32_t n = (uint32_t)s->n_pairs;
   const uint32_t nbt = nblk(n, kRsTile);
-  const bool tiles = (s->lp.L & 7u) == 0u;
+  // Sorting the levels apart needs no pass over the level bits, but its tiles take pairs of several
+  // training blocks, so the first pass counts its digits itself: worth it where a whole pass (27 us
+  // at 2^21 pairs, the count 5) is saved, and possible where a level's pairs fill whole tiles.  A
+  // step of 16 levels x 2^13 entries took 236 us by the full key, 209 by level
+  const bool by_level = (s->entry_bits + 7u) / 8u < (s->key_bits + 7u) / 8u && (s->B * 8u) % kRsTile == 0u;
+  const bool tiles = (s->lp.L & 7u) == 0u && !by_level;
   k_train<<<tblocks, 64 * kTrainWaves, sizeof(TrainSmem), st>>>(s->lp, s->batch, s->B, off, stride, s->grid_h, s->wb, S,
                                                               s->mlp_part, s->lpart, s->acc, s->scales + 3, log2T,
-                                                              s->pkeys[0], s->pvals[0], nbt, s->rs_hist);
+                                                              s->pkeys[0], s->pvals[0], nbt, s->rs_hist, by_level);
   timer_end(c, "learned_train", st, ev);
   k_reduce_mlp<<<dim3(kMlpParams / 256, kRedGroups), 256, 0, st>>>(s->mlp_part, tblocks, s->mlp_part2);
   // the encoding gradient: pairs sorted by entry, summed per entry in a fixed order
   timer_begin(c, "learned_grad_sort", st, &ev);
   int which = 0;
-  hipError_t e = radix_sort<float2>(s->pkeys, s->pvals, n, s->key_bits, s->rs_hist, st, which, tiles);
+  hipError_t e = radix_sort<float2>(s->pkeys, s->pvals, n, by_level ? s->entry_bits : s->key_bits, s->rs_hist, st,
+                                    which, tiles, by_level ? s->lp.L : 1u);
   timer_end(c, "learned_grad_sort", st, ev);
   if (e != hipSuccess) return e;
   const uint32_t nt = nblk(n, kGredTile);
