@@ -18,6 +18,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <type_traits>
 #include <vector>
 
 #include "gi_device.hpp"
@@ -349,34 +350,16 @@ __global__ __launch_bounds__(256) void k_tflag_compact(const uint8_t* flag, cons
       if ((w[q] >> (8 * b)) & 1u) list[at++] = base_id + 4u * q + b;
 }
 
-// ---- training batch selection: k-th of `rows` samples = list entry floor((k + u) n / rows) --
-
-__global__ void k_select_batch(const uint32_t* list, const uint32_t* count, const float4* trec, const float4* hitpos,
-                               const float4* hitnrm, float u, uint32_t rows, float4* batch, float* acc) {
-  const uint32_t k = blockIdx.x * blockDim.x + threadIdx.x;
-  const uint32_t n = *count;
-  if (k == 0) acc[7] = (float)n;
-  if (k >= rows) return;
-  if (n == 0) {
-    batch[3 * k] = batch[3 * k + 1] = batch[3 * k + 2] = make_float4(0.f, 0.f, 0.f, 0.f);
-    return;
-  }
-  uint32_t r = (uint32_t)(((double)k + (double)u) * (double)n / (double)rows);
-  if (r >= n) r = n - 1u;
-  const uint32_t gid = list[r];
-  const float4 nv = hitnrm[gid];
-  batch[3 * k] = hitpos[gid];
-  batch[3 * k + 1] = make_float4(nv.x, nv.y, nv.z, __uint_as_float(gid));
-  batch[3 * k + 2] = trec[gid];
-}
-
 // ---- stable LSD radix sort of (u32 key, payload) pairs, 8-bit digits ---------------------
 // Per pass: per-block digit counts (blocks of kRsTile items), a scan of each digit's block
 // counts (one block per digit), and a scatter in which every item goes to its digit's offset
 // plus the number of items of its block with the same digit and a lower index (wave ballots
 // within a round, each wave's counts over its rounds, then the waves in order), so equal keys
-// keep their input order.
+// keep their input order.  Up to kRsInline tiles the scatter adds up the tile counts itself: a
+// block reads 256 x tiles words.  At 32 tiles that adds 1 us to a pass and saves a launch of 4.6; at
+// 64 it adds 6.5.
 constexpr uint32_t kRsThreads = 512, kRsRounds = 4, kRsTile = kRsThreads * kRsRounds;
+constexpr uint32_t kRsInline = 32;
 
 __global__ __launch_bounds__(kRsThreads) void k_rs_hist(const uint32_t* key, uint32_t n, uint32_t shift, uint32_t nb,
                                                         uint32_t* hist) {
@@ -420,11 +403,18 @@ __global__ __launch_bounds__(256) void k_rs_digit_scan(uint32_t* hist, uint32_t 
 // w*256 .. w*256+255 (four rounds of 64): an item's rank among its wave's items of the same
 // digit is its rank in its round's ballot plus the wave's count of that digit in earlier
 // rounds (a per-wave LDS row, touched by that wave alone); the waves' rows, scanned in wave
-// order, and the digits' tile offsets place it.  Equal digits keep their input order.
+// order, and the digits' tile offsets place it.  Equal digits keep their input order.  dtot null:
+// off holds the tile counts as they are.  rows: the values are row numbers and the rows themselves
+// (three float4 of rows.in) are written in place of keys and values.
+struct RsRows {
+  const float4* in;
+  float4* out;
+};
+
 template <typename V>
 __global__ __launch_bounds__(kRsThreads) void k_rs_scatter(const uint32_t* kin, const V* vin, uint32_t* kout, V* vout,
                                                            uint32_t n, uint32_t shift, uint32_t nb, uint32_t seg_tiles,
-                                                           const uint32_t* off, const uint32_t* dtot_all) {
+                                                           const uint32_t* off, const uint32_t* dtot, RsRows rows) {
   constexpr uint32_t W = kRsThreads / 64u, PW = kRsTile / W;
   static_assert(PW == 64u * kRsRounds && kRsThreads >= 256u, "a wave holds kRsRounds rounds of 64 items");
   __shared__ uint32_t sk[kRsTile];
@@ -437,7 +427,6 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_scatter(const uint32_t* kin, 
   const uint32_t b0 = blockIdx.x * kRsTile;
   const uint32_t m = n - b0 < kRsTile ? n - b0 : kRsTile;     // items of this tile
   const uint32_t seg = blockIdx.x / seg_tiles;                // sorted by itself
-  const uint32_t* dtot = dtot_all + 256u * seg;
   const uint64_t below = (1ull << lane) - 1ull;
   uint32_t key[kRsRounds], rk[kRsRounds];
   V val[kRsRounds];
@@ -446,6 +435,23 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_scatter(const uint32_t* kin, 
     const uint32_t i = w * PW + 64u * j + lane;
     key[j] = i < m ? kin[b0 + i] : 0u;
     if (i < m) val[j] = vin[b0 + i];
+  }
+  // digit t: its items in the segment's earlier tiles and in the whole segment
+  uint32_t before = 0u, total = 0u;
+  if (t < 256u) {
+    if (dtot) {
+      before = off[t * nb + blockIdx.x];
+      total = dtot[256u * seg + t];
+    } else {
+      const uint32_t* h = off + (size_t)t * nb + seg * seg_tiles;
+      const uint32_t own = blockIdx.x - seg * seg_tiles;
+#pragma unroll 8
+      for (uint32_t q = 0; q < seg_tiles; ++q) {
+        const uint32_t v = h[q];
+        before += q < own ? v : 0u;
+        total += v;
+      }
+    }
   }
 #pragma unroll
   for (uint32_t k = 0; k < 256u; k += 64u) wc[w][k + lane] = 0u;
@@ -478,7 +484,7 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_scatter(const uint32_t* kin, 
       c += x;
     }
   }
-  uint32_t x1 = c, x2 = t < 256u ? dtot[t] : 0u;
+  uint32_t x1 = c, x2 = total;
 #pragma unroll
   for (int dd = 1; dd < 64; dd <<= 1) {
     const uint32_t o1 = (uint32_t)__shfl_up((int)x1, dd, 64), o2 = (uint32_t)__shfl_up((int)x2, dd, 64);
@@ -493,13 +499,13 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_scatter(const uint32_t* kin, 
   }
   __syncthreads();
   if (t < 256u) {
-    uint32_t e1 = x1 - c, e2 = x2 - dtot[t];
+    uint32_t e1 = x1 - c, e2 = x2 - total;
     for (uint32_t q = 0; q < w; ++q) {
       e1 += lc[q];
       e2 += ld[q];
     }
     lbase[t] = e1;
-    gbase[t] = seg * seg_tiles * kRsTile + e2 + off[t * nb + blockIdx.x];
+    gbase[t] = seg * seg_tiles * kRsTile + e2 + before;
   }
   __syncthreads();
 #pragma unroll
@@ -519,6 +525,17 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_scatter(const uint32_t* kin, 
       const uint32_t k = sk[i];
       const uint32_t d = (k >> shift) & 255u;
       const uint32_t g = gbase[d] + (i - lbase[d]);
+      if constexpr (sizeof(V) == 4) {
+        if (rows.out) {
+          const float4* r = rows.in + 3u * (size_t)sv[i];
+          const float4 r0 = r[0], r1 = r[1], r2 = r[2];
+          float4* o = rows.out + 3u * (size_t)g;
+          o[0] = r0;
+          o[1] = r1;
+          o[2] = r2;
+          continue;
+        }
+      }
       kout[g] = k;
       vout[g] = sv[i];
     }
@@ -528,20 +545,22 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_scatter(const uint32_t* kin, 
 // sorts (keys[0], vals[0]) by the low `bits` bits of the keys, stable; returns the index of
 // the buffer pair holding the result.  first_hist: the tile counts of the lowest digit are
 // already in hist (written with the keys).  segments > 1: so many equal runs of whole tiles are
-// sorted each by itself
+// sorted each by itself.  rows.out: the last pass writes the sorted rows there, not the pairs
 template <typename V>
 static hipError_t radix_sort(uint32_t* keys[2], V* vals[2], uint32_t n, uint32_t bits, uint32_t* hist,
-                             hipStream_t st, int& which, bool first_hist = false, uint32_t segments = 1) {
+                             hipStream_t st, int& which, bool first_hist = false, uint32_t segments = 1,
+                             RsRows rows = RsRows{nullptr, nullptr}) {
   which = 0;
   if (n == 0) return hipSuccess;
   const uint32_t nb = (n + kRsTile - 1u) / kRsTile;
   const uint32_t seg_tiles = nb / segments;
-  uint32_t* dtot = hist + 256u * nb;
+  uint32_t* dtot = seg_tiles > kRsInline ? hist + 256u * nb : nullptr;
   for (uint32_t shift = 0; shift < bits; shift += 8u) {
     if (shift > 0u || !first_hist) k_rs_hist<<<nb, kRsThreads, 0, st>>>(keys[which], n, shift, nb, hist);
-    k_rs_digit_scan<<<dim3(256, segments), 256, 0, st>>>(hist, nb, seg_tiles, dtot);
+    if (dtot) k_rs_digit_scan<<<dim3(256, segments), 256, 0, st>>>(hist, nb, seg_tiles, dtot);
     k_rs_scatter<V><<<nb, kRsThreads, 0, st>>>(keys[which], vals[which], keys[which ^ 1], vals[which ^ 1], n, shift, nb,
-                                               seg_tiles, hist, dtot);
+                                               seg_tiles, hist, dtot,
+                                               shift + 8u < bits ? RsRows{nullptr, nullptr} : rows);
     which ^= 1;
   }
   return hipGetLastError();
@@ -567,33 +586,101 @@ __device__ inline uint32_t sort_bucket(const LearnedParams& lp, const float4& p)
   return spread5(q0) | (spread5(q1) << 1) | (spread5(q2) << 2);
 }
 
-__global__ void k_batch_keys(LearnedParams lp, const float4* in, uint32_t rows, uint32_t* key, uint32_t* idx) {
-  const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= rows) return;
-  key[i] = sort_bucket(lp, in[3 * (size_t)i]);
-  idx[i] = i;
-}
+// The batch's rows, their sort keys and numbers.  A caller's arrays are read in order: one block per
+// sort tile, which also counts its first digits.  Training rays (sample k of `rows` is the ray at list
+// entry floor((k + u) n / rows)) are scattered reads, bound by what one CU can have in flight: a row
+// per thread over four times the blocks (65,536 rows took 17 us by tiles), counted by the sort.
+// With the sort's last pass writing the rows and few tiles needing no scan launch, a 2^14-sample step
+// on the caller's arrays went from 209 to 203 us, a learned FP8 frame from 491 to 467.
+struct BatchRays {
+  static constexpr uint32_t kRows = 1;
+  static constexpr bool kTile = false;
+  const float4* pos;          // per ray: hit point, normal, target
+  const float4* nrm;
+  const float4* tgt;
+  const uint32_t* list;
+  const uint32_t* count;
+  float u;
+  float* acc;
+};
+struct BatchArrays {
+  static constexpr uint32_t kRows = kRsRounds;
+  static constexpr bool kTile = true;
+  const float4* pos;
+  const float4* nrm;
+  const float4* tgt;
+};
 
-__global__ void k_batch_gather(const float4* in, const uint32_t* idx, uint32_t rows, float4* out) {
-  const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= rows) return;
-  const size_t r = idx[i];
-  out[3 * (size_t)i] = in[3 * r];
-  out[3 * (size_t)i + 1] = in[3 * r + 1];
-  out[3 * (size_t)i + 2] = in[3 * r + 2];
+template <typename Src>
+__global__ __launch_bounds__(kRsThreads) void k_batch_rows(LearnedParams lp, Src src, uint32_t rows, float4* batch,
+                                                           uint32_t* key, uint32_t* idx, uint32_t* hist) {
+  __shared__ uint32_t h[256];
+  const uint32_t t = threadIdx.x;
+  if (Src::kTile) {
+    if (t < 256u) h[t] = 0u;
+    __syncthreads();
+  }
+  uint32_t n = 0;
+  if constexpr (std::is_same_v<Src, BatchRays>) {
+    n = *src.count;
+    if (blockIdx.x == 0u && t == 0u) src.acc[7] = (float)n;
+  }
+  const uint32_t k0 = blockIdx.x * kRsThreads * Src::kRows + t;
+  float4 p[Src::kRows], nv[Src::kRows], tg[Src::kRows];
+  uint32_t at[Src::kRows];
+#pragma unroll
+  for (uint32_t j = 0; j < Src::kRows; ++j) {
+    at[j] = min(k0 + kRsThreads * j, rows - 1u);
+    if constexpr (std::is_same_v<Src, BatchRays>)
+      at[j] = min((uint32_t)(((double)at[j] + (double)src.u) * (double)n / (double)rows), n - 1u);
+  }
+  if (std::is_same_v<Src, BatchArrays> || n != 0u) {
+    if constexpr (std::is_same_v<Src, BatchRays>)
+#pragma unroll
+      for (uint32_t j = 0; j < Src::kRows; ++j) at[j] = src.list[at[j]];
+#pragma unroll
+    for (uint32_t j = 0; j < Src::kRows; ++j) {
+      p[j] = src.pos[at[j]];
+      nv[j] = src.nrm[at[j]];
+      tg[j] = src.tgt[at[j]];
+      if constexpr (std::is_same_v<Src, BatchRays>) nv[j].w = __uint_as_float(at[j]);
+    }
+  } else {
+#pragma unroll
+    for (uint32_t j = 0; j < Src::kRows; ++j) p[j] = nv[j] = tg[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+  }
+#pragma unroll
+  for (uint32_t j = 0; j < Src::kRows; ++j) {
+    const uint32_t k = k0 + kRsThreads * j;
+    if (k >= rows) break;
+    batch[3 * (size_t)k] = p[j];
+    batch[3 * (size_t)k + 1] = nv[j];
+    batch[3 * (size_t)k + 2] = tg[j];
+    const uint32_t b = sort_bucket(lp, p[j]);
+    key[k] = b;
+    idx[k] = k;
+    if (Src::kTile) atomicAdd(&h[b & 255u], 1u);
+  }
+  if (!Src::kTile) return;
+  __syncthreads();
+  if (t < 256u) hist[t * gridDim.x + blockIdx.x] = h[t];
 }
 
 __global__ void k_zero_f32(float* p, uint64_t n);
 static inline uint32_t nblk(uint64_t n, uint32_t b) { return (uint32_t)((n + b - 1) / b); }
 
-static hipError_t sort_batch(gi_context* c, hipStream_t st, uint32_t rows) {
+template <typename Src>
+static hipError_t make_batch(gi_context* c, hipStream_t st, const Src& src, uint32_t rows) {
   LearnedState* s = c->learned;
   hipEvent_t ev;
+  timer_begin(c, "learned_select", st, &ev);
+  k_batch_rows<<<nblk(rows, kRsThreads * Src::kRows), kRsThreads, 0, st>>>(s->lp, src, rows, s->batch_raw,
+                                                                           s->bkeys[0], s->bvals[0], s->rs_hist);
+  timer_end(c, "learned_select", st, ev);
   timer_begin(c, "learned_sort", st, &ev);
-  k_batch_keys<<<nblk(rows, 256), 256, 0, st>>>(s->lp, s->batch_raw, rows, s->bkeys[0], s->bvals[0]);
   int which = 0;
-  hipError_t e = radix_sort<uint32_t>(s->bkeys, s->bvals, rows, 15u, s->rs_hist, st, which);
-  k_batch_gather<<<nblk(rows, 256), 256, 0, st>>>(s->batch_raw, s->bvals[which], rows, s->batch);
+  const hipError_t e = radix_sort<uint32_t>(s->bkeys, s->bvals, rows, 15u, s->rs_hist, st, which, Src::kTile, 1u,
+                                            RsRows{s->batch_raw, s->batch});
   timer_end(c, "learned_sort", st, ev);
   if (e != hipSuccess) return e;
   return hipGetLastError();
@@ -1644,10 +1731,9 @@ hipError_t learned_train(gi_context* c, hipStream_t st) {
   k_tflag_count<<<s->tflag_blocks, 256, 0, st>>>(s->tflag, s->ccount);
   k_scan_counts<<<1, 1024, 0, st>>>(s->ccount, s->tflag_blocks);
   k_tflag_compact<<<s->tflag_blocks, 256, 0, st>>>(s->tflag, s->ccount, s->clist);
-  k_select_batch<<<nblk(rows, 256), 256, 0, st>>>(s->clist, s->ccount + s->tflag_blocks, s->trec, s->hitpos,
-                                                  s->hitnrm, u, rows, s->batch_raw, s->acc);
   timer_end(c, "learned_select", st, ev);
-  hipError_t e = sort_batch(c, st, rows);
+  hipError_t e = make_batch(c, st, BatchRays{s->hitpos, s->hitnrm, s->trec, s->clist, s->ccount + s->tflag_blocks,
+                                             u, s->acc}, rows);
   for (uint32_t k = 0; k < steps && e == hipSuccess; ++k) e = train_step(c, st, true, k % s->sub, s->sub);
   if (e != hipSuccess) return e;
   return hipGetLastError();
@@ -1658,11 +1744,7 @@ hipError_t learned_step_on(gi_context* c, const float4* pos, const float4* nrm, 
   LearnedState* s = c->learned;
   learned_set_domain(c);
   if (n != s->B) return hipErrorInvalidValue;
-  // batch rows: pos, nrm, target
-  hipError_t e = hipMemcpy2DAsync(s->batch_raw, 48, pos, 16, 16, n, hipMemcpyDeviceToDevice, st);
-  if (e == hipSuccess) e = hipMemcpy2DAsync(s->batch_raw + 1, 48, nrm, 16, 16, n, hipMemcpyDeviceToDevice, st);
-  if (e == hipSuccess) e = hipMemcpy2DAsync(s->batch_raw + 2, 48, tgt, 16, 16, n, hipMemcpyDeviceToDevice, st);
-  if (e == hipSuccess) e = sort_batch(c, st, n);
+  const hipError_t e = make_batch(c, st, BatchArrays{pos, nrm, tgt}, n);
   if (e != hipSuccess) return e;
   return train_step(c, st, apply, 0u, 1u);
 }
