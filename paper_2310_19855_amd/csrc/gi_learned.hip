@@ -1081,8 +1081,8 @@ __device__ inline void adam_lazy(float graw, float& p, float& m, float& v, const
 // kGredItems (t + 1) - 1 (one pair per thread: 256-pair tiles, whose many blocks overlap one
 // another's loads).  Each thread sums its pairs in order, restarting where the key changes; a segmented scan over the
 // threads (fixed association) extends every pair's sum back to the tile start or to its
-// entry's first pair.  MODE 0 records each tile's last partial sum and whether its entry began
-// inside the tile.  In MODE 1 and 2 a tile's carry-in (the sums, in earlier tiles, of the entry
+// entry's first pair.  k_gred_tails records each tile's last partial sum and whether its entry
+// began inside the tile.  In k_gred a tile's carry-in (the sums, in earlier tiles, of the entry
 // open at its start) is the run of those tail sums from the tile where that entry began,
 // added oldest first; MODE 1 adds the carry to entries that began in an earlier tile and, at each
 // entry's last pair, takes the lazy Adam step of its two parameters (none when the step's
@@ -1091,15 +1091,78 @@ __device__ inline void adam_lazy(float graw, float& p, float& m, float& v, const
 constexpr uint32_t kGredItems = 1, kGredTile = 256 * kGredItems;
 static_assert(kGredItems <= 32, "a thread's key changes fit one word");
 
+// A wave per tile: the tile's last sum needs the scan at one pair only, and of the scan's inputs
+// those back to the entry's first pair, so the tile's last 64 pairs nearly always hold it (the
+// rest is read, in the scan's own association, where no entry begins in them).  Against the
+// whole tile's scan: 14 -> 6 us at 2^21 pairs, both tables (2^13 and 2^19 entries a level).
+__global__ __launch_bounds__(256) void k_gred_tails(const uint32_t* key, const float2* val, uint32_t n, uint32_t tiles,
+                                                    float2* tail_sum, uint32_t* tail_in, float* acc, MlpFinish mf) {
+  static_assert(kGredTile == 256, "four runs of 64 pairs");
+  reduce_mlp_finish(mf, acc);
+  const uint32_t lane = threadIdx.x & 63u, tile = 4u * blockIdx.x + (threadIdx.x >> 6);
+  if (tile >= tiles) return;
+  struct Run {
+    float2 s;
+    bool f;
+  };
+  // the inclusive scan at the tile's pair 64 q + 62 over its last 64 pairs (63 in the first run):
+  // lane l holds pair 64 q - 1 + l; f: an entry begins among them
+  const auto run = [&](uint32_t q) {
+    const bool in = q > 0u || lane > 0u;
+    const uint32_t i = in ? tile * kGredTile + 64u * q - 1u + lane : n;
+    const uint32_t k = i < n ? key[i] : 0xFFFFFFFFu;
+    const uint32_t kp = i > 0u && i - 1u < n ? key[i - 1u] : 0xFFFFFFFFu;
+    const float2 w = i < n ? val[i] : make_float2(0.0f, 0.0f);
+    float2 s = make_float2(0.0f + w.x, 0.0f + w.y);
+    int f = k != kp ? 1 : 0;
+#pragma unroll
+    for (uint32_t d = 1; d < 64u; d <<= 1) {
+      const float ox = __shfl_up(s.x, d, 64), oy = __shfl_up(s.y, d, 64);
+      const int of = __shfl_up(f, d, 64);
+      if (lane >= d + (q == 0u ? 1u : 0u) && !f) {
+        s.x = ox + s.x;
+        s.y = oy + s.y;
+        f = of;
+      }
+    }
+    return Run{make_float2(__shfl(s.x, 63, 64), __shfl(s.y, 63, 64)), __shfl(f, 63, 64) != 0};
+  };
+  const auto join = [](const Run& o, Run& r) {
+    r.s = make_float2(o.s.x + r.s.x, o.s.y + r.s.y);
+    r.f = o.f;
+  };
+  const uint32_t e = tile * kGredTile + kGredTile - 1u;
+  const uint32_t ke = e < n ? key[e] : 0xFFFFFFFFu;
+  const uint32_t kp = e - 1u < n ? key[e - 1u] : 0xFFFFFFFFu;
+  const float2 w = e < n ? val[e] : make_float2(0.0f, 0.0f);
+  float2 sum = make_float2(0.0f + w.x, 0.0f + w.y);
+  bool began = ke != kp;
+  if (!began) {
+    Run r = run(3u);
+    if (!r.f) join(run(2u), r);
+    if (!r.f) {
+      Run o = run(1u);
+      if (!o.f) join(run(0u), o);
+      join(o, r);
+    }
+    sum = make_float2(r.s.x + sum.x, r.s.y + sum.y);
+    began = r.f;
+  }
+  if (lane == 0u) {
+    tail_sum[tile] = sum;
+    tail_in[tile] = began ? 1u : 0u;
+  }
+}
+
 template <int MODE>
-__global__ __launch_bounds__(256) void k_gred(const uint32_t* key, const float2* val, uint32_t n, float2* tail_sum,
-                                              uint32_t* tail_in, float* gstate, __half* ph, float* gdense, AdamArgs a,
-                                              float* acc, MlpFinish mf) {
+__global__ __launch_bounds__(256) void k_gred(const uint32_t* key, const float2* val, uint32_t n,
+                                              const float2* tail_sum, const uint32_t* tail_in, float* gstate,
+                                              __half* ph, float* gdense, AdamArgs a, const float* acc) {
   __shared__ float2 cs[2][256];
   __shared__ uint32_t cf[2][256];
   __shared__ float2 cin_s;
   const uint32_t t = threadIdx.x;
-  if (MODE != 0 && t < 64u) {
+  if (t < 64u) {
     // wave 0: the carry-in.  Walk back over the earlier tiles' flags, 64 at a time, to the
     // nearest tile whose last entry began inside it (tile 0's always did), then add the tail
     // sums from that tile up to this one's predecessor in tile order.
@@ -1188,16 +1251,6 @@ __global__ __launch_bounds__(256) void k_gred(const uint32_t* key, const float2*
   }
   const float2 carry = t > 0 ? cs[cur][t - 1] : make_float2(0.0f, 0.0f);
   const bool carry_in_tile = t > 0 && cf[cur][t - 1] != 0u;
-  if (MODE == 0) {
-    reduce_mlp_finish(mf, acc);
-    if (t == 255u) {
-      const uint32_t j = kGredItems - 1;
-      const bool own = (heads >> j) & 1u;
-      tail_sum[blockIdx.x] = own ? loc[j] : make_float2(carry.x + loc[j].x, carry.y + loc[j].y);
-      tail_in[blockIdx.x] = (own || carry_in_tile) ? 1u : 0u;
-    }
-    return;
-  }
   const float2 cin = cin_s;
   const bool skip = MODE == 1 && acc[1] != 0.0f;
   float gx[kGredItems], gy[kGredItems];
@@ -1692,14 +1745,14 @@ static hipError_t train_step(gi_context* c, hipStream_t st, bool apply, uint32_t
   }
   const MlpFinish mf{s->mlp_part2, s->lpart, tblocks, s->mlp_g};
   timer_begin(c, "learned_grad_apply", st, &ev);
-  k_gred<0><<<nt, 256, 0, st>>>(s->pkeys[which], s->pvals[which], n, s->tail_sum, s->tail_in, s->gstate, s->grid_h,
-                                s->grid_g, ag, s->acc, mf);
+  k_gred_tails<<<nblk(nt, 4), 256, 0, st>>>(s->pkeys[which], s->pvals[which], n, nt, s->tail_sum, s->tail_in, s->acc,
+                                            mf);
   if (apply)
     k_gred<1><<<nt, 256, 0, st>>>(s->pkeys[which], s->pvals[which], n, s->tail_sum, s->tail_in, s->gstate, s->grid_h,
-                                  s->grid_g, ag, s->acc, mf);
+                                  s->grid_g, ag, s->acc);
   else
     k_gred<2><<<nt, 256, 0, st>>>(s->pkeys[which], s->pvals[which], n, s->tail_sum, s->tail_in, s->gstate, s->grid_h,
-                                  s->grid_g, ag, s->acc, mf);
+                                  s->grid_g, ag, s->acc);
   timer_end(c, "learned_grad_apply", st, ev);
   if (apply) {
     AdamArgs am = ag;

@@ -58,3 +58,28 @@ def test_every_level_gets_its_own_gradient(levels, tlog2, blog2):
         assert abs(np.linalg.norm(got[l]) / np.linalg.norm(ref) - 1) < 0.01, l
         assert not got[l][(ref == 0).all(1)].any(), l
     ctx.close()
+
+
+@pytest.mark.parametrize("counts", [(1024,), (700, 90, 33, 201), (63, 64, 65, 128, 192, 255, 257), (1, 1023)])
+def test_long_runs_of_one_entry_sum_over_tiles(counts):
+    """Samples in a few points: an entry's pairs run over parts of one 256-pair tile, all of it,
+    and several, so that a tile's last entry begins in each of its four runs of 64 or before it."""
+    levels, tlog2, blog2 = 4, 12, 10
+    assert sum(counts) <= 1 << blog2
+    spec = OL.Spec(levels=levels, table_log2=tlog2)
+    ctx, sc, lo, hi = _ctx(mlp_levels=levels, mlp_table_log2=tlog2, mlp_batch_log2=blog2)
+    pos, nrm, tgt = _samples(1 << blog2, lo, hi, seed=len(counts))
+    at = 0
+    for c in counts:
+        pos[at:at + c] = pos[at]
+        at += c
+    tp, tn, tt = (torch.from_numpy(a).cuda() for a in (pos, nrm, tgt))
+    ctx.learned_step(tp, tn, tt, apply=False)
+    torch.cuda.synchronize()
+    got = _unpack(ctx, spec)["grid_g"].reshape(levels, spec.T, 2) / 128.0
+    x32 = OL.normalize_pos(pos[:, :3], lo, hi)
+    g = _grid_gradient(spec, OL.init_params(spec, SEED), x32, nrm[:, :3], tgt[:, :3])
+    for l in range(levels):
+        assert _cos(got[l], g[l]) > 0.999, l
+        assert abs(np.linalg.norm(got[l]) / np.linalg.norm(g[l]) - 1) < 0.01, l
+    ctx.close()
