@@ -350,6 +350,49 @@ __global__ __launch_bounds__(256) void k_tflag_compact(const uint8_t* flag, cons
       if ((w[q] >> (8 * b)) & 1u) list[at++] = base_id + 4u * q + b;
 }
 
+// ---- deterministic sum of the training blocks' weight-gradient partials (fixed order) -----
+// Stage 1: block b sums the partials of run b / kRedCols (kRedGroups consecutive runs of training
+// blocks) for 512 parameters, four slices of the run (one float4 column per thread) added in a
+// fixed order; stage 2 (reduce_mlp_finish) adds the runs in order and flags non-finite gradients.
+// Stage 1 rides in the launch of the gradient sort's first scatter, whose blocks it does not
+// depend on (as a launch of its own it took 4.8 us a step).
+struct MlpPartials {
+  const float* part;      // null: nothing to sum
+  uint32_t parts;
+  float* part2;
+};
+constexpr uint32_t kRedCols = kMlpParams / 512;
+static_assert(kMlpParams % 512 == 0, "a block's 128 float4 columns are all in range");
+
+__device__ inline void reduce_mlp_part(const MlpPartials& mp, uint32_t b, float4 (*red)[128]) {
+  const uint32_t l = threadIdx.x & 127u, slice = threadIdx.x >> 7;
+  const uint32_t c4 = (b % kRedCols) * 128u + l, run = b / kRedCols;    // float4 column
+  const uint32_t per = (mp.parts + kRedGroups - 1u) / kRedGroups;
+  const uint32_t w0 = run * per, w1 = w0 + per < mp.parts ? w0 + per : mp.parts;
+  const float4* p4 = reinterpret_cast<const float4*>(mp.part);
+  float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+  for (uint32_t w = w0 + slice; w < w1; w += 4u) {
+    const float4 v = p4[(size_t)w * (kMlpParams / 4) + c4];
+    s.x += v.x;
+    s.y += v.y;
+    s.z += v.z;
+    s.w += v.w;
+  }
+  red[slice][l] = s;
+  __syncthreads();
+  if (slice != 0u) return;
+  float4 t = red[0][l];
+#pragma unroll
+  for (int k = 1; k < 4; ++k) {
+    const float4 v = red[k][l];
+    t.x += v.x;
+    t.y += v.y;
+    t.z += v.z;
+    t.w += v.w;
+  }
+  reinterpret_cast<float4*>(mp.part2 + (size_t)run * kMlpParams)[c4] = t;
+}
+
 // ---- stable LSD radix sort of (u32 key, payload) pairs, 8-bit digits ---------------------
 // Per pass: per-block digit counts (blocks of kRsTile items), a scan of each digit's block
 // counts (one block per digit), and a scatter in which every item goes to its digit's offset
@@ -405,7 +448,7 @@ __global__ __launch_bounds__(256) void k_rs_digit_scan(uint32_t* hist, uint32_t 
 // rounds (a per-wave LDS row, touched by that wave alone); the waves' rows, scanned in wave
 // order, and the digits' tile offsets place it.  Equal digits keep their input order.  dtot null:
 // off holds the tile counts as they are.  rows: the values are row numbers and the rows themselves
-// (three float4 of rows.in) are written in place of keys and values.
+// (three float4 of rows.in) are written in place of keys and values.  Blocks from nb on: mp.
 struct RsRows {
   const float4* in;
   float4* out;
@@ -414,15 +457,21 @@ struct RsRows {
 template <typename V>
 __global__ __launch_bounds__(kRsThreads) void k_rs_scatter(const uint32_t* kin, const V* vin, uint32_t* kout, V* vout,
                                                            uint32_t n, uint32_t shift, uint32_t nb, uint32_t seg_tiles,
-                                                           const uint32_t* off, const uint32_t* dtot, RsRows rows) {
+                                                           const uint32_t* off, const uint32_t* dtot, RsRows rows,
+                                                           MlpPartials mp) {
   constexpr uint32_t W = kRsThreads / 64u, PW = kRsTile / W;
   static_assert(PW == 64u * kRsRounds && kRsThreads >= 256u, "a wave holds kRsRounds rounds of 64 items");
-  __shared__ uint32_t sk[kRsTile];
+  __shared__ __align__(16) uint32_t sk[kRsTile];
   __shared__ V sv[kRsTile];
   __shared__ uint32_t wc[W][256];      // per wave: digit counts, then their prefix over earlier waves
   __shared__ uint32_t lbase[256];      // local position of each digit's first item
   __shared__ uint32_t gbase[256];      // global position of each digit's first item of this tile
   __shared__ uint32_t lc[W], ld[W];
+  static_assert(kRsThreads == 512 && sizeof(sk) == 512 * sizeof(float4), "the partials' sums");
+  if (blockIdx.x >= nb) {
+    reduce_mlp_part(mp, blockIdx.x - nb, reinterpret_cast<float4 (*)[128]>(sk));
+    return;
+  }
   const uint32_t t = threadIdx.x, lane = t & 63u, w = t >> 6;
   const uint32_t b0 = blockIdx.x * kRsTile;
   const uint32_t m = n - b0 < kRsTile ? n - b0 : kRsTile;     // items of this tile
@@ -545,11 +594,12 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_scatter(const uint32_t* kin, 
 // sorts (keys[0], vals[0]) by the low `bits` bits of the keys, stable; returns the index of
 // the buffer pair holding the result.  first_hist: the tile counts of the lowest digit are
 // already in hist (written with the keys).  segments > 1: so many equal runs of whole tiles are
-// sorted each by itself.  rows.out: the last pass writes the sorted rows there, not the pairs
+// sorted each by itself.  rows.out: the last pass writes the sorted rows there, not the pairs.
+// mp.part: the first scatter's launch also sums the weight-gradient partials
 template <typename V>
 static hipError_t radix_sort(uint32_t* keys[2], V* vals[2], uint32_t n, uint32_t bits, uint32_t* hist,
                              hipStream_t st, int& which, bool first_hist = false, uint32_t segments = 1,
-                             RsRows rows = RsRows{nullptr, nullptr}) {
+                             RsRows rows = RsRows{nullptr, nullptr}, MlpPartials mp = MlpPartials{nullptr, 0u, nullptr}) {
   which = 0;
   if (n == 0) return hipSuccess;
   const uint32_t nb = (n + kRsTile - 1u) / kRsTile;
@@ -558,9 +608,10 @@ static hipError_t radix_sort(uint32_t* keys[2], V* vals[2], uint32_t n, uint32_t
   for (uint32_t shift = 0; shift < bits; shift += 8u) {
     if (shift > 0u || !first_hist) k_rs_hist<<<nb, kRsThreads, 0, st>>>(keys[which], n, shift, nb, hist);
     if (dtot) k_rs_digit_scan<<<dim3(256, segments), 256, 0, st>>>(hist, nb, seg_tiles, dtot);
-    k_rs_scatter<V><<<nb, kRsThreads, 0, st>>>(keys[which], vals[which], keys[which ^ 1], vals[which ^ 1], n, shift, nb,
+    const uint32_t extra = shift == 0u && mp.part ? kRedCols * kRedGroups : 0u;
+    k_rs_scatter<V><<<nb + extra, kRsThreads, 0, st>>>(keys[which], vals[which], keys[which ^ 1], vals[which ^ 1], n, shift, nb,
                                                seg_tiles, hist, dtot,
-                                               shift + 8u < bits ? RsRows{nullptr, nullptr} : rows);
+                                               shift + 8u < bits ? RsRows{nullptr, nullptr} : rows, mp);
     which ^= 1;
   }
   return hipGetLastError();
@@ -998,42 +1049,6 @@ void k_train(LearnedParams lp, const float4* batch, uint32_t B, uint32_t off, ui
   }
 }
 
-// deterministic sum of the per-block partials (fixed order) -> gradient; flags non-finite.
-// Stage 1: block (x, y) sums the partials of run y (kRedGroups consecutive runs of training
-// blocks) for 256 parameters, four slices of the run (one float4 column per thread) added in
-// a fixed order; stage 2 (reduce_mlp_finish) adds the runs in order.
-__global__ __launch_bounds__(256) void k_reduce_mlp(const float* part, uint32_t parts, float* part2) {
-  __shared__ float4 red[4][64];
-  const uint32_t l = threadIdx.x & 63u, slice = threadIdx.x >> 6;
-  const uint32_t c4 = blockIdx.x * 64u + l;                    // float4 column
-  const uint32_t per = (parts + kRedGroups - 1u) / kRedGroups;
-  const uint32_t w0 = blockIdx.y * per, w1 = w0 + per < parts ? w0 + per : parts;
-  const float4* p4 = reinterpret_cast<const float4*>(part);
-  float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
-  if (c4 < kMlpParams / 4)
-    for (uint32_t w = w0 + slice; w < w1; w += 4u) {
-      const float4 v = p4[(size_t)w * (kMlpParams / 4) + c4];
-      s.x += v.x;
-      s.y += v.y;
-      s.z += v.z;
-      s.w += v.w;
-    }
-  red[slice][l] = s;
-  __syncthreads();
-  if (slice == 0u && c4 < kMlpParams / 4) {
-    float4 t = red[0][l];
-#pragma unroll
-    for (int k = 1; k < 4; ++k) {
-      const float4 v = red[k][l];
-      t.x += v.x;
-      t.y += v.y;
-      t.z += v.z;
-      t.w += v.w;
-    }
-    reinterpret_cast<float4*>(part2 + (size_t)blockIdx.y * kMlpParams)[c4] = t;
-  }
-}
-
 // stage 2, run by the blocks of the first pass over the sorted grid pairs (which comes after
 // stage 1 and before any reader of the gradient or of the flags)
 struct MlpFinish {
@@ -1074,6 +1089,35 @@ __device__ inline void adam_lazy(float graw, float& p, float& m, float& v, const
   v = a.b2 * v + (1.0f - a.b2) * gi * gi;
   const float mh = m / a.c1, vh = v / a.c2;
   p = p - a.lr * mh / (sqrtf(vh) + a.eps);
+}
+
+// Adam on the MLP weights, one parameter per thread (dense; skipped when the step's gradients are
+// not finite), and the weights' BF16 copies; the e4m3 copies, which need every weight's new value
+// for their scales, follow in k_mlp_step.  Run by k_gred's blocks past its tiles: the two steps
+// share nothing but their inputs (as a launch of its own this took 4.8 us a step).
+struct MlpAdam {
+  float* p;
+  const float* g;
+  float* m;
+  float* v;
+  __bf16* wb;
+  AdamArgs a;
+};
+
+__device__ inline void mlp_adam(const MlpAdam& ma, uint32_t i, const float* acc) {
+  if (i >= (uint32_t)kMlpParams) return;
+  const AdamArgs& a = ma.a;
+  float w = ma.p[i];
+  if (acc[1] == 0.0f) {
+    const float gi = ma.g[i] * a.inv_scale;
+    const float mi = a.b1 * ma.m[i] + (1.0f - a.b1) * gi;
+    const float vi = a.b2 * ma.v[i] + (1.0f - a.b2) * gi * gi;
+    ma.m[i] = mi;
+    ma.v[i] = vi;
+    w = w - a.lr * (mi / a.c1) / (sqrtf(vi / a.c2) + a.eps);
+    ma.p[i] = w;
+  }
+  mlp_bf16_copy((int)i, w, ma.wb);
 }
 
 // ---- per-entry sums of the sorted gradient pairs, then the grid step --------------------
@@ -1157,11 +1201,16 @@ __global__ __launch_bounds__(256) void k_gred_tails(const uint32_t* key, const f
 template <int MODE>
 __global__ __launch_bounds__(256) void k_gred(const uint32_t* key, const float2* val, uint32_t n,
                                               const float2* tail_sum, const uint32_t* tail_in, float* gstate,
-                                              __half* ph, float* gdense, AdamArgs a, const float* acc) {
+                                              __half* ph, float* gdense, AdamArgs a, const float* acc,
+                                              MlpAdam ma) {
   __shared__ float2 cs[2][256];
   __shared__ uint32_t cf[2][256];
   __shared__ float2 cin_s;
   const uint32_t t = threadIdx.x;
+  if (MODE == 1 && blockIdx.x * kGredTile >= n) {
+    mlp_adam(ma, 256u * (blockIdx.x - (n + kGredTile - 1u) / kGredTile) + t, acc);
+    return;
+  }
   if (t < 64u) {
     // wave 0: the carry-in.  Walk back over the earlier tiles' flags, 64 at a time, to the
     // nearest tile whose last entry began inside it (tile 0's always did), then add the tail
@@ -1278,29 +1327,6 @@ __global__ __launch_bounds__(256) void k_gred(const uint32_t* key, const float2*
       gs[2u * (size_t)k[j] + 1u] = vz[j];
       *reinterpret_cast<__half2*>(ph + 2u * (size_t)k[j]) = __halves2half2(__float2half(pm[j].x), __float2half(pm[j].y));
     }
-}
-
-// end of an applied step (one block of 1024 threads): Adam on the MLP weights, their bf16 and
-// e4m3 working copies, the e4m3 activation scales of the step's batch, the step's statistics
-// Adam on the MLP weights (dense), one parameter per thread
-// the MLP's Adam step (skipped when the step's loss was not finite) and the weights' BF16
-// copies; the e4m3 copies, which need every weight's new value for their scales, follow in
-// k_mlp_step
-__global__ __launch_bounds__(256) void k_mlp_adam(float* p, const float* g, float* m, float* v, AdamArgs a,
-                                                  const float* acc, __bf16* wb) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= kMlpParams) return;
-  float w = p[i];
-  if (acc[1] == 0.0f) {
-    const float gi = g[i] * a.inv_scale;
-    const float mi = a.b1 * m[i] + (1.0f - a.b1) * gi;
-    const float vi = a.b2 * v[i] + (1.0f - a.b2) * gi * gi;
-    m[i] = mi;
-    v[i] = vi;
-    w = w - a.lr * (mi / a.c1) / (sqrtf(vi / a.c2) + a.eps);
-    p[i] = w;
-  }
-  mlp_bf16_copy(i, w, wb);
 }
 
 // fp8: the e4m3 copies and scales are formed only for FP8 inference (no other reader)
@@ -1723,12 +1749,12 @@ static hipError_t train_step(gi_context* c, hipStream_t st, bool apply, uint32_t
                                                               s->mlp_part, s->lpart, s->acc, s->scales + 3, log2T,
                                                               s->pkeys[0], s->pvals[0], nbt, s->rs_hist, by_level);
   timer_end(c, "learned_train", st, ev);
-  k_reduce_mlp<<<dim3(kMlpParams / 256, kRedGroups), 256, 0, st>>>(s->mlp_part, tblocks, s->mlp_part2);
   // the encoding gradient: pairs sorted by entry, summed per entry in a fixed order
   timer_begin(c, "learned_grad_sort", st, &ev);
   int which = 0;
   hipError_t e = radix_sort<float2>(s->pkeys, s->pvals, n, by_level ? s->entry_bits : s->key_bits, s->rs_hist, st,
-                                    which, tiles, by_level ? s->lp.L : 1u);
+                                    which, tiles, by_level ? s->lp.L : 1u, RsRows{nullptr, nullptr},
+                                    MlpPartials{s->mlp_part, tblocks, s->mlp_part2});
   timer_end(c, "learned_grad_sort", st, ev);
   if (e != hipSuccess) return e;
   const uint32_t nt = nblk(n, kGredTile);
@@ -1747,19 +1773,18 @@ static hipError_t train_step(gi_context* c, hipStream_t st, bool apply, uint32_t
   timer_begin(c, "learned_grad_apply", st, &ev);
   k_gred_tails<<<nblk(nt, 4), 256, 0, st>>>(s->pkeys[which], s->pvals[which], n, nt, s->tail_sum, s->tail_in, s->acc,
                                             mf);
+  MlpAdam ma{s->mlp, s->mlp_g, s->mlp_m, s->mlp_v, s->wb, ag};
+  ma.a.lr = c->cfg.mlp_lr_mlp;
+  ma.a.eps = 1e-8f;
   if (apply)
-    k_gred<1><<<nt, 256, 0, st>>>(s->pkeys[which], s->pvals[which], n, s->tail_sum, s->tail_in, s->gstate, s->grid_h,
-                                  s->grid_g, ag, s->acc);
+    k_gred<1><<<nt + nblk(kMlpParams, 256), 256, 0, st>>>(s->pkeys[which], s->pvals[which], n, s->tail_sum, s->tail_in,
+                                                          s->gstate, s->grid_h, s->grid_g, ag, s->acc, ma);
   else
     k_gred<2><<<nt, 256, 0, st>>>(s->pkeys[which], s->pvals[which], n, s->tail_sum, s->tail_in, s->gstate, s->grid_h,
-                                  s->grid_g, ag, s->acc);
+                                  s->grid_g, ag, s->acc, ma);
   timer_end(c, "learned_grad_apply", st, ev);
   if (apply) {
-    AdamArgs am = ag;
-    am.lr = c->cfg.mlp_lr_mlp;
-    am.eps = 1e-8f;
     timer_begin(c, "learned_adam", st, &ev);
-    k_mlp_adam<<<nblk(kMlpParams, 256), 256, 0, st>>>(s->mlp, s->mlp_g, s->mlp_m, s->mlp_v, am, s->acc, s->wb);
     k_mlp_step<<<1, 1024, 0, st>>>(s->mlp, s->acc, s->w8, s->scales, c->d_stats,
                                    c->cfg.cache_mode == GI_CACHE_MLP_FP8);
     timer_end(c, "learned_adam", st, ev);
