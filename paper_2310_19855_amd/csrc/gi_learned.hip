@@ -82,7 +82,7 @@ struct LearnedState {
   size_t n_pairs = 0;
   uint32_t key_bits = 0;         // bits of a gradient pair key (level * T + entry)
   uint32_t entry_bits = 0;       // bits of its entry alone
-  float* lpart = nullptr;        // [train_blocks] loss partials
+  float4* lpart = nullptr;       // [train_blocks] loss partials, largest input and activations
   float2* judge_part = nullptr;  // per-wave (error, norm) partials of the judge
   uint32_t B = 0;
   uint32_t sub = 1;              // sub-batches held by the frame's batch (rows = sub * B)
@@ -763,10 +763,6 @@ __device__ inline void store_tile(const f32x4_t& v, __bf16* M, int ld, __bf16* M
   }
 }
 
-__device__ inline void atomic_max_abs(float* p, float v) {
-  atomicMax(reinterpret_cast<unsigned int*>(p), __float_as_uint(fabsf(v)));
-}
-
 // sample i of the step is row off + stride * i of the batch array.  The encoding gradient is
 // written as (level * T + entry, corner weight * dX) pairs, to be sorted and summed per entry:
 // no float atomics, so the step is deterministic.  Group g (samples 32 g .. 32 g + 31) fills
@@ -781,7 +777,7 @@ static_assert(64 * kTrainWaves == 32 * kMaxLevels, "one thread of a training blo
 // 4 waves per SIMD (two blocks per CU, as the LDS tiles allow) caps the registers at 128
 __global__ __launch_bounds__(64 * kTrainWaves) __attribute__((amdgpu_waves_per_eu(4)))
 void k_train(LearnedParams lp, const float4* batch, uint32_t B, uint32_t off, uint32_t stride, const __half* grid_h,
-             const __bf16* wb, float loss_scale, float* part, float* lpart, float* acc, float* amax, uint32_t log2T,
+             const __bf16* wb, float loss_scale, float* part, float4* lpart, float* acc, uint32_t log2T,
              uint32_t* pkey, float2* pval, uint32_t nb, uint32_t* hist, bool by_level) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   TrainSmem& S = *reinterpret_cast<TrainSmem*>(smem_raw);
@@ -1042,10 +1038,9 @@ void k_train(LearnedParams lp, const float4* batch, uint32_t B, uint32_t off, ui
       b1 = fmaxf(b1, red[q][2]);
       b2 = fmaxf(b2, red[q][3]);
     }
-    lpart[blockIdx.x] = l * inv3b;
-    atomic_max_abs(&amax[0], bx);
-    atomic_max_abs(&amax[1], b1);
-    atomic_max_abs(&amax[2], b2);
+    // (the maxima by atomics, on one cache line and from blocks that end together, took k_train from
+    // 22 to 33 us at 16 x 2^13 and from 26 to 35 at 16 x 2^19 entries)
+    lpart[blockIdx.x] = make_float4(l * inv3b, bx, b1, b2);
   }
 }
 
@@ -1053,18 +1048,36 @@ void k_train(LearnedParams lp, const float4* batch, uint32_t B, uint32_t off, ui
 // stage 1 and before any reader of the gradient or of the flags)
 struct MlpFinish {
   const float* part2;
-  const float* lpart;
+  const float4* lpart;
   uint32_t parts;
   float* g;
+  float* amax;
 };
 
 __device__ inline void reduce_mlp_finish(const MlpFinish& mf, float* acc) {
   if (blockIdx.x == 0 && threadIdx.x < 64) {
-    // the step's loss: lane j sums partials j, j + 64, ... in order, then a fixed butterfly
-    float l = 0.0f;
-    for (uint32_t w = threadIdx.x; w < mf.parts; w += 64u) l += mf.lpart[w];
-    for (int o = 32; o >= 1; o >>= 1) l += __shfl_xor(l, o, 64);
-    if (threadIdx.x == 0) acc[0] = l;
+    // the step's loss: lane j sums partials j, j + 64, ... in order, then a fixed butterfly;
+    // and its activation ranges
+    float l = 0.0f, a0 = 0.0f, a1 = 0.0f, a2 = 0.0f;
+    for (uint32_t w = threadIdx.x; w < mf.parts; w += 64u) {
+      const float4 v = mf.lpart[w];
+      l += v.x;
+      a0 = fmaxf(a0, v.y);
+      a1 = fmaxf(a1, v.z);
+      a2 = fmaxf(a2, v.w);
+    }
+    for (int o = 32; o >= 1; o >>= 1) {
+      l += __shfl_xor(l, o, 64);
+      a0 = fmaxf(a0, __shfl_xor(a0, o, 64));
+      a1 = fmaxf(a1, __shfl_xor(a1, o, 64));
+      a2 = fmaxf(a2, __shfl_xor(a2, o, 64));
+    }
+    if (threadIdx.x == 0) {
+      acc[0] = l;
+      mf.amax[0] = fmaxf(mf.amax[0], a0);
+      mf.amax[1] = fmaxf(mf.amax[1], a1);
+      mf.amax[2] = fmaxf(mf.amax[2], a2);
+    }
   }
   for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < (uint32_t)kMlpParams; i += gridDim.x * blockDim.x) {
     float t = mf.part2[i];
@@ -1746,7 +1759,7 @@ static hipError_t train_step(gi_context* c, hipStream_t st, bool apply, uint32_t
   const bool by_level = (s->entry_bits + 7u) / 8u < (s->key_bits + 7u) / 8u && (s->B * 8u) % kRsTile == 0u;
   const bool tiles = (s->lp.L & 7u) == 0u && !by_level;
   k_train<<<tblocks, 64 * kTrainWaves, sizeof(TrainSmem), st>>>(s->lp, s->batch, s->B, off, stride, s->grid_h, s->wb, S,
-                                                              s->mlp_part, s->lpart, s->acc, s->scales + 3, log2T,
+                                                              s->mlp_part, s->lpart, s->acc, log2T,
                                                               s->pkeys[0], s->pvals[0], nbt, s->rs_hist, by_level);
   timer_end(c, "learned_train", st, ev);
   // the encoding gradient: pairs sorted by entry, summed per entry in a fixed order
@@ -1769,7 +1782,7 @@ static hipError_t train_step(gi_context* c, hipStream_t st, bool apply, uint32_t
     ag.lr = c->cfg.mlp_lr_grid;
     ag.eps = 1e-15f;
   }
-  const MlpFinish mf{s->mlp_part2, s->lpart, tblocks, s->mlp_g};
+  const MlpFinish mf{s->mlp_part2, s->lpart, tblocks, s->mlp_g, s->scales + 3};
   timer_begin(c, "learned_grad_apply", st, &ev);
   k_gred_tails<<<nblk(nt, 4), 256, 0, st>>>(s->pkeys[which], s->pvals[which], n, nt, s->tail_sum, s->tail_in, s->acc,
                                             mf);
