@@ -1318,9 +1318,10 @@ __global__ __launch_bounds__(kTraceBlock) void k_shade_hits(SceneView sv, ShadeT
   if ((uint32_t)__ffsll((long long)same) - 1u == (threadIdx.x & 63u)) {
     // two 64-bit atomics (r | g << 32, b | count << 32) instead of four 32-bit ones: the pass is
     // bound by the rate of its atomics where many cells are hit (4K field, 485 -> 408 us; 480x270
-    // room with bounces 61 -> 52; 64 lights at 1281x717 293 -> 263; field at 1080 170 -> 161).  A low word that wraps carries one
-    // into the high word; the lane whose addition wrapped it takes that one back, so the four
-    // sums end as if added apart, and the high words' wraps count net of it
+    // room with bounces 61 -> 52; 64 lights at 1281x717 293 -> 263; field at 1080 170 -> 161).
+    // A low word that wraps carries one into the high word; the lane whose addition wrapped it
+    // takes that one back, so the four sums end as if added apart, and the high words' wraps
+    // count net of it
     unsigned long long* accp = reinterpret_cast<unsigned long long*>(c.acc + slot);
     const unsigned long long a0 = (unsigned long long)g0 | ((unsigned long long)g1 << 32);
     const unsigned long long a1 = (unsigned long long)g2 | ((unsigned long long)__popcll(same) << 32);
