@@ -681,16 +681,11 @@ __device__ inline int32_t table_insert(const CacheArgs& c, uint64_t key, bool& i
 // slot that the fingerprint names, on to the next one inside the bucket while another cell is
 // there.  No read goes before it, and cells of one bucket start at different slots, where all of
 // them claimed its first empty slot and all but one failed (38 -> 16 us for the claims of the pass below)
-__device__ inline int32_t table_insert_empty(const CacheArgs& c, uint64_t key, bool& inserted) {
+__device__ inline int32_t table_insert_empty(const CacheArgs& c, uint64_t key) {
   const uint32_t first = bucket_of(key, c.bucket_mask) * kBucket, f = fingerprint_of(key);
-  inserted = false;
   for (uint32_t k = 0; k < kBucket; ++k) {
     const uint32_t s = first + ((f + k) & (kBucket - 1u));
     const uint32_t prev = atomicCAS(c.fp + s, 0u, f);
-    if (prev == 0u) {
-      c.key[s] = key;
-      inserted = true;
-    }
     if (prev == 0u || prev == f) return (int32_t)s;
   }
   return -1;
@@ -1101,8 +1096,10 @@ __global__ __launch_bounds__(64) void k_light_grid(ShadeTables st, uint32_t n_em
 // bid for a place by the hash of their cell alone, an atomic minimum with no search; the winner of
 // a place inserts its cell and stores (the lowest ray of a place is the lowest of its cell), and
 // the other rays of that cell are done.  Only the rays of a cell that lost its place to another
-// cell (one or two in a hundred: sixteen places per table slot) insert and bid for their slot.  Three
-// passes, 51 us together with the clearing.
+// cell (one or two in a hundred: sixteen places per table slot) insert and bid for their slot.  Cells
+// of one fingerprint have one place, so where two of them share a slot the place's winner is the
+// lowest ray of both: it stores whether or not the other cell was inserted first, and its claim keeps
+// the other cell's rays out.  Three passes, 51 us together with the clearing.
 __global__ __launch_bounds__(256) void k_restir_clear(uint32_t* fp, uint64_t* key, uint32_t* claim, uint32_t n,
                                                       uint32_t* place, uint32_t places) {
   const uint32_t i = blockIdx.x * 256u + threadIdx.x;
@@ -1114,7 +1111,7 @@ __global__ __launch_bounds__(256) void k_restir_clear(uint32_t* fp, uint64_t* ke
 }
 
 __device__ inline uint32_t restir_place(const RestirArgs& ra, uint64_t key) {
-  return hash_xxh32((uint32_t)key + hash_xxh32((uint32_t)(key >> 32))) & ra.place_mask;
+  return fingerprint_of(key) & ra.place_mask;
 }
 
 __global__ __launch_bounds__(256) void k_restir_bid(const uint4* rec, uint32_t n, RestirArgs ra) {
@@ -1124,6 +1121,15 @@ __global__ __launch_bounds__(256) void k_restir_bid(const uint4* rec, uint32_t n
   if (*p > gid) atomicMin(p, gid);     // bids only fall: a lower one, however old the read, settles it
 }
 
+// ray gid's cell and reservoir into slot s, by the one ray that the slot keeps
+__device__ inline void restir_keep(const RestirArgs& ra, uint32_t gid, int32_t s, float4* yw, float4* nrm,
+                                   uint32_t* cnt) {
+  ra.next.key[s] = ra.r_key[gid];
+  yw[s] = ra.r_yw[gid];
+  nrm[s] = ra.r_n[gid];
+  cnt[s] = ra.r_m[gid];
+}
+
 __global__ __launch_bounds__(256) void k_restir_claim(const uint4* rec, uint32_t n, RestirArgs ra, float4* yw,
                                                       float4* nrm, uint32_t* cnt) {
   const uint32_t gid = blockIdx.x * 256u + threadIdx.x;
@@ -1131,16 +1137,14 @@ __global__ __launch_bounds__(256) void k_restir_claim(const uint4* rec, uint32_t
   const uint64_t key = ra.r_key[gid];
   const uint32_t w = ra.place[restir_place(ra, key)];
   int32_t slot = -1;
-  bool inserted;
   if (w == gid) {
-    const int32_t s = table_insert_empty(ra.next, key, inserted);
-    if (inserted) {       // else the bucket is full, or holds another cell of this fingerprint
-      yw[s] = ra.r_yw[gid];
-      nrm[s] = ra.r_n[gid];
-      cnt[s] = ra.r_m[gid];
+    const int32_t s = table_insert_empty(ra.next, key);
+    if (s >= 0) {         // else the bucket is full
+      atomicMin(ra.claim + s, gid);
+      restir_keep(ra, gid, s, yw, nrm, cnt);
     }
   } else if (ra.r_key[w] != key) {
-    slot = table_insert_empty(ra.next, key, inserted);
+    slot = table_insert_empty(ra.next, key);
     if (slot >= 0) atomicMin(ra.claim + slot, gid);
   }
   ra.r_slot[gid] = slot;
@@ -1152,10 +1156,7 @@ __global__ __launch_bounds__(256) void k_restir_store(const uint4* rec, uint32_t
   if (gid >= n || !(rec[gid].w & GI_RAY_HIT)) return;
   if (ra.r_m[gid] == 0u) return;
   const int32_t s = ra.r_slot[gid];
-  if (s < 0 || ra.claim[s] != gid) return;
-  yw[s] = ra.r_yw[gid];
-  nrm[s] = ra.r_n[gid];
-  cnt[s] = ra.r_m[gid];
+  if (s >= 0 && ra.claim[s] == gid) restir_keep(ra, gid, s, yw, nrm, cnt);
 }
 
 template <int STACK>
