@@ -291,7 +291,8 @@ struct SceneView {
 // 1 + 2^-16) is never below it: with c = -(o * inv) rounded, both carry errors of at most
 // 2^-22 |c| beside relative ones of a few 2^-24, and |c| 2^-21 is taken off the near constant
 // and added to the far one.  A plane at infinity or an origin too large for c gives NaN or an
-// infinity on the accepting side, which the minimum and maximum skip.
+// infinity on the accepting side, which the minimum and maximum skip.  From |c| = 3e38 on the far
+// constant, which is c widened, could overflow where c does not: infinite slack accepts that axis.
 struct Slabs {
   float nx, ny, nz;         // 1 / direction
   float fx, fy, fz;         // 1 / direction, times 1 + 2^-16
@@ -306,7 +307,8 @@ __device__ inline Slabs make_slabs(const RayQ& r) {
   s.nx = r.ix; s.ny = r.iy; s.nz = r.iz;
   s.fx = r.ix * kFar; s.fy = r.iy * kFar; s.fz = r.iz * kFar;
   const float cx = -(r.ox * r.ix), cy = -(r.oy * r.iy), cz = -(r.oz * r.iz);
-  const float ex = fabsf(cx) * kSlack, ey = fabsf(cy) * kSlack, ez = fabsf(cz) * kSlack;
+  const auto slack = [](float c) { return fabsf(c) > 3.0e38f ? __builtin_inff() : fabsf(c) * kSlack; };
+  const float ex = slack(cx), ey = slack(cy), ez = slack(cz);
   s.cnx = cx - ex; s.cny = cy - ey; s.cnz = cz - ez;
   s.cfx = fmaf(cx, kFar, ex); s.cfy = fmaf(cy, kFar, ey); s.cfz = fmaf(cz, kFar, ez);
   s.ox = r.ix < 0.0f ? 16u : 0u;
