@@ -220,9 +220,11 @@ struct RayQ {
 
 __device__ inline float sel3(float a, float b, float c, int k) { return k == 0 ? a : (k == 1 ? b : c); }
 
+constexpr float kMinDir = 1e-30f;   // smaller direction components are cut off for the box tests
+
 __device__ inline float safe_inv(float d) {
   float dd = d;
-  if (fabsf(dd) < 1e-30f) dd = dd < 0.0f ? -1e-30f : 1e-30f;
+  if (fabsf(dd) < kMinDir) dd = dd < 0.0f ? -kMinDir : kMinDir;
   return 1.0f / dd;
 }
 
@@ -317,13 +319,19 @@ __device__ inline Slabs make_slabs(const RayQ& r) {
   return s;
 }
 
-// true if the ray may enter the box [lo, hi] at or before tcull
+// true if the ray may enter the box [lo, hi] at or before tcull.  An axis whose direction safe_inv
+// cut off is left out: the ray may run in a face of the box (a plane at 0 against an origin at 0 has
+// no slack), or along a tiny direction to distances that the cut-off reciprocal understates
 __device__ inline bool enter_box(const Slabs& s, float4 lo, float4 hi, float tcull) {
-  const bool px = s.nx < 0.0f, py = s.ny < 0.0f, pz = s.nz < 0.0f;
-  const float tn = fmaxf(fmaxf(fmaf(px ? hi.x : lo.x, s.nx, s.cnx), fmaf(py ? hi.y : lo.y, s.ny, s.cny)),
-                         fmaxf(fmaf(pz ? hi.z : lo.z, s.nz, s.cnz), 0.0f));
-  const float tf = fminf(fminf(fmaf(px ? lo.x : hi.x, s.fx, s.cfx), fmaf(py ? lo.y : hi.y, s.fy, s.cfy)),
-                         fmaf(pz ? lo.z : hi.z, s.fz, s.cfz));
+  float tn = 0.0f, tf = __builtin_inff();
+  const auto axis = [&](float n, float f, float cn, float cf, float l, float h) {
+    const bool in = fabsf(n) < 1.0f / kMinDir;
+    tn = fmaxf(tn, in ? fmaf(n < 0.0f ? h : l, n, cn) : 0.0f);
+    tf = fminf(tf, in ? fmaf(n < 0.0f ? l : h, f, cf) : __builtin_inff());
+  };
+  axis(s.nx, s.fx, s.cnx, s.cfx, lo.x, hi.x);
+  axis(s.ny, s.fy, s.cny, s.cfy, lo.y, hi.y);
+  axis(s.nz, s.fz, s.cnz, s.cfz, lo.z, hi.z);
   return tn <= tf && tn <= tcull;
 }
 
