@@ -991,7 +991,7 @@ __global__ __launch_bounds__(1024) void k_lg_box_final(const uint32_t* part, uin
 // Light lists, one wave per grid cell: each light's importance (mean over the cell's 8
 // corners of luminance * area * cos / max(d^2, area); culled when the cell's bounding sphere
 // lies behind the light's plane or beyond its range sqrt(luminance * area / threshold) plus
-// the radius) into LDS, then lgrid_k rounds of the largest importance > 0 (ties: lower index).
+// the radius) into LDS, then the lgrid_k largest above 0 in descending order (ties: lower index).
 constexpr uint32_t kLgMaxLights = 2048;
 
 __global__ __launch_bounds__(64) void k_light_grid(ShadeTables st, uint32_t n_emit, float threshold, uint32_t* list,
@@ -1006,6 +1006,7 @@ __global__ __launch_bounds__(64) void k_light_grid(ShadeTables st, uint32_t n_em
 #pragma unroll
   for (int j = 0; j < 3; ++j) cc[j] = g.lo[j] + ((float)cxyz[j] + 0.5f) * g.h;
   const float R = g.h * 0.8660254037844386f;
+  uint32_t positive = 0;
   for (uint32_t k = lane; k < n_emit; k += 64u) {
     const float4 A = st.evert[3 * k], B = st.evert[3 * k + 1], C = st.evert[3 * k + 2];
     const float cen[3] = {(float)((((double)A.x + (double)B.x) + (double)C.x) / 3.0),
@@ -1032,16 +1033,21 @@ __global__ __launch_bounds__(64) void k_light_grid(ShadeTables st, uint32_t n_em
       v = s * 0.125f;
     }
     imp[k] = v;
+    positive += (uint32_t)__popcll(__ballot(v > 0.0f));
   }
   __syncthreads();
-  const uint32_t K = st.lg_k < n_emit ? st.lg_k : n_emit;
+  positive = (uint32_t)__builtin_amdgcn_readfirstlane((int)positive);   // lane 0 is in every turn
+  const uint32_t K = st.lg_k < positive ? st.lg_k : positive;
+  if (lane == 0u) count[ci] = K;
   // Two ways to the same list.  Ranks: a light's place is the number of lights before it in the
   // order (about 3 instructions for each pair of lights, n^2 / 64 pairs a lane); rounds: K times the
   // largest one left (3 n / 64 instructions a lane and about 90 for the wave's maximum).  The
-  // smaller count decides: 128 lights in lists of 64 took 58 us by rounds and 16 by ranks
-  // (2,048 cells)
+  // smaller count decides, with the K lights that this cell really keeps.  Measured over 2,048 cells,
+  // all ranks against one round: 2.0 and 0.72 us for 64 lights, 8.3 and 0.80 for 128, 32 and 0.91
+  // for 256, 125 and 1.18 for 512: they cross at 3, 10, 35 and 106 kept lights, where the counts say 4,
+  // 12, 37 and 118.  128 lights in lists of 64: 59 us by rounds, 17 by ranks; 512 lights of which a
+  // cell keeps 3, in lists of 256: 53 by rounds, 144 by ranks
   if (3u * n_emit * (n_emit / 64u + 1u) < K * (3u * (n_emit / 64u + 1u) + 90u)) {
-    uint32_t positive = 0;
     for (uint32_t k0 = 0; k0 < n_emit; k0 += 64u) {
       const uint32_t k = k0 + lane;
       const float v = k < n_emit ? imp[k] : -1.0f;
@@ -1051,12 +1057,9 @@ __global__ __launch_bounds__(64) void k_light_grid(ShadeTables st, uint32_t n_em
         rank += (x > v || (x == v && i < k)) ? 1u : 0u;
       }
       if (v > 0.0f && rank < K) list[(size_t)ci * st.lg_k + rank] = k;
-      positive += (uint32_t)__popcll(__ballot(v > 0.0f));
     }
-    if (lane == 0u) count[ci] = positive < K ? positive : K;
     return;
   }
-  uint32_t cnt = 0;
   for (uint32_t r = 0; r < K; ++r) {
     float bv = -1.0f;
     uint32_t bi = 0xFFFFFFFFu;
@@ -1077,15 +1080,12 @@ __global__ __launch_bounds__(64) void k_light_grid(ShadeTables st, uint32_t n_em
         bi = oi;
       }
     }
-    if (bi == 0xFFFFFFFFu) break;
     if (lane == 0u) {
-      list[(size_t)ci * st.lg_k + cnt] = bi;
+      list[(size_t)ci * st.lg_k + r] = bi;
       imp[bi] = -1.0f;
     }
-    ++cnt;
     __syncthreads();
   }
-  if (lane == 0u) count[ci] = cnt;
 }
 
 // World-space reservoirs (Section 2.3.1): the table written this frame starts empty; after the
