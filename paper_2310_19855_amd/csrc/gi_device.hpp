@@ -289,12 +289,14 @@ struct SceneView {
 
 // Slab terms of one ray.  Along an axis a plane p lies at p * inv - o * inv, one fused
 // multiply-add from the ray's constants; the sign of inv tells which plane of a box is the near
-// one.  The near plane's value never exceeds the true distance and the far plane's (times
-// 1 + 2^-16) is never below it: with c = -(o * inv) rounded, both carry errors of at most
-// 2^-22 |c| beside relative ones of a few 2^-24, and |c| 2^-21 is taken off the near constant
-// and added to the far one.  A plane at infinity or an origin too large for c gives NaN or an
-// infinity on the accepting side, which the minimum and maximum skip.  From |c| = 3e38 on the far
-// constant, which is c widened, could overflow where c does not: infinite slack accepts that axis.
+// one.  With c = -(o * inv) rounded, a plane's value carries errors of at most 2^-22 |c| beside
+// relative ones of a few 2^-24.  |c| 2^-21 is taken off the near constant and added to the far one,
+// which covers the former (nothing is taken off where c is 0); the latter are covered by the far
+// planes' factor 1 + 2^-16 where near is compared with far, and by the factor 1.0001221 of every
+// tcull where near is compared with a hit.  All three margins are needed for a box to be missed only
+// if the ray misses it.  A plane at infinity or an origin too large for c gives NaN or an infinity on
+// the accepting side, which the minimum and maximum skip.  From |c| = 3e38 on the far constant, which
+// is c widened, could overflow where c does not: infinite slack accepts that axis.
 struct Slabs {
   float nx, ny, nz;         // 1 / direction
   float fx, fy, fz;         // 1 / direction, times 1 + 2^-16

@@ -192,7 +192,10 @@ hipError_t launch_count_traversal(gi_context* c, unsigned long long* out, hipStr
 constexpr size_t kNoAllocScratchWords = (size_t)4 << 20;
 constexpr int kMaxDevices = 64;
 hipError_t scratch_init(int device);
-// places the rays of a reservoir cell bid for: sixteen per table slot, at most 2^22
+// places the rays of a reservoir cell bid for: sixteen per table slot, at most 2^22.  They follow the
+// table, not the frame.  Shading and reservoirs together, with the insertions in the shading and with
+// bids (2^16 slots): 36 and 42 us for one probe of one ray, 48 and 48 for 64 rays, 54 and 51 for
+// 1,024, 322 and 171 for 460,000
 inline uint32_t restir_places(uint32_t restir_log2) { return 1u << (restir_log2 < 18u ? restir_log2 + 4u : 22u); }
 uint32_t noalloc_chunk_rays(uint32_t spill_rows);
 hipError_t launch_trace_rays_noalloc(gi_context* c, const float4* o, const float4* d, uint32_t n, uint32_t any,
